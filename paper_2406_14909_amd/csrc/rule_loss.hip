@@ -4,23 +4,30 @@
 //     dl[h][r] = sum over blocks (I, J) of masked_r(I, J) * ebar[h][I][J],
 // where masked_r(I, J) counts the pairs (i, j) of the 64 x 64 block with
 // j <= i, j >= s and j < band_start_r(i) (every token of a block carries the
-// block's mean).  masked_r depends on the rule and the block only, in closed
-// form: with the block band the band start is constant over the block's rows;
-// with the token band it moves by one per row, and the row sum is an
-// arithmetic series clipped to [0, block width].  Also writes each rule's
-// density (paper Sec. 4 "Setups": in-memory KV-cache length over sequence
-// length during decoding), kv_len / n, with kv_len = min(s + w, n) the tokens
-// the rule's token-exact cache holds once n tokens have been seen.
+// block's mean).
 //
-// One work-group per head; lane r of every wave handles rule r; the 4 waves
-// take interleaved block rows and meet in LDS.  Sums are fp64.
+// Between whole blocks past the sinks masked_r depends on the distance
+// k = I - J alone, so the profile is first folded along its diagonals, for all
+// rules at once: D[k] = sum of ebar[I][I - k].  Two lines of blocks count
+// differently and are kept aside, also by distance: the block column that
+// holds the sink edge (C[k]) and a last block row of fewer than 64 tokens
+// (L[k]).  A rule of band length w masks every block at distance
+// k >= k_full completely, k_full = ceil((w + 63) / 64) (w blocks with the
+// block band), and with the token band the two distances before it in part;
+// so with suffix sums of the three lines it costs three lookups and at most
+// seven closed-form counts.  Sums are fp64.
+//
+// What bounds it: reading the lower triangle once (1024 heads at n = 8192:
+// 33.8 MB in 10.0 us, 3.4 TB/s) and, below about 10 MB, the start and the end
+// of a work-group.  Each element costs one load, one conversion and one fp64
+// add; an earlier version scanned every block row in fp64 and evaluated every
+// rule on it, which the vector ALUs bounded (44.0 us).
 #include "moa_device.h"
 
 namespace moa {
 
 namespace {
 
-constexpr int kWaves = 4;
 constexpr int kBlock = kInfluenceBlock;
 
 // sum_{x = 0}^{t} clamp(x, 0, m) for 0 <= m <= 64 and |t| < 2^20
@@ -46,14 +53,6 @@ __device__ __forceinline__ int masked_in_block(int I, int J, int n, int s, int w
   return clamp_prefix(r1 - 1 + a, m) - clamp_prefix(r0 - 1 + a, m);
 }
 
-// Per block row I, the blocks a rule masks completely form one range
-// [ja, jb] (ja: first block past the sinks; jb: last block below the band
-// start of the row block's first row), so their sum is rows(I) times a
-// difference of the row's prefix sums of cols(J) * ebar[I][J].  At most three
-// blocks are masked in part: the block holding the sink edge and, with the
-// token band, the two blocks the band edge sweeps across; those use the
-// closed-form count.  Each wave takes every fourth block row: its lanes load
-// the row, scan it (fp64) into the wave's LDS strip, then act as rules.
 // DPP move of an fp64 value (both halves with the same control); lanes with
 // no source, or in rows outside row_mask, receive 0.
 template <int ctrl, int row_mask>
@@ -84,118 +83,143 @@ __device__ __forceinline__ double lane63(double v) {
   return __builtin_bit_cast(double, (uint64_t(hi) << 32) | lo);
 }
 
-template <int kChunks>   // 64-block chunks per row (covers nb <= 64 * kChunks)
-__global__ void __launch_bounds__(kWaves * 64) rule_loss_kernel(RuleLossArgs a) {
-  __shared__ double s_pre[kWaves][kChunks * 64];     // prefix sums of one row per wave
-  __shared__ float s_raw[kWaves][kChunks * 64];      // the row itself
-  __shared__ double s_dl[kWaves][kMaxRules];
-  const int lane = threadIdx.x & 63;
-  const int wave = threadIdx.x >> 6;
+// One work-group per head.  Thread t folds distance k = t % kDist of block
+// rows t / kDist + m * (threads / kDist): consecutive lanes read consecutive
+// elements of a row, and kDepth rows are in flight per thread.
+template <int kThreads, int kDist, int kDepth>   // kDist: power of two >= nb, <= kThreads
+__global__ void __launch_bounds__(kThreads) rule_loss_kernel(RuleLossArgs a) {
+  constexpr int kGroups = kThreads / kDist;
+  static_assert(kGroups >= 1 && kDist % 64 == 0, "thread mapping");
+  __shared__ double s_d[kGroups][kDist];       // diagonal sums; row 0: of all block rows
+  __shared__ double s_suf[3][kDist + 64];      // suffix sums of D, C, L (0 from nb on)
+  __shared__ float s_line[2][kDist];           // C and L
+  __shared__ double s_part[3][kMaxRules];
+  const int t = static_cast<int>(threadIdx.x);
+  const int lane = t & 63, wave = t >> 6;
   const int h = static_cast<int>(blockIdx.x);
-  const int nb = a.nb, n = a.n, s = a.num_sink;
-  const bool rule_ok = lane < a.num_rules;
-  const int w = rule_ok ? a.window[lane] : 1;
+  const int nb = a.nb, n = a.n, s = a.num_sink, bsh = a.band_shift;
   const float* e = a.ebar + int64_t(h) * nb * nb;
-  double* pre = s_pre[wave];
-  float* raw = s_raw[wave];
-  const int ja = (s + kBlock - 1) / kBlock;                  // first block with no sink column
-  const int js = (s % kBlock) ? s / kBlock : -1;             // block holding the sink edge, if any
-  double acc = 0.0;
+  const int ja = (s + kBlock - 1) / kBlock;              // first block with no sink column
+  const int js = (s % kBlock) ? s / kBlock : nb;         // block column of the sink edge (nb: none)
+  const int rows_last = n - (nb - 1) * kBlock;
+  const int nbw = rows_last == kBlock ? nb : nb - 1;     // block rows of 64 tokens
 
-  // The wave's rows I = wave + kWaves * k are processed in groups of kDepth;
-  // the next group is loaded into registers (lane holds J = 64 c + lane)
-  // while the current one is scanned and used, so kDepth rows are in flight.
-  constexpr int kDepth = kChunks >= 8 ? 2 : 16 / kChunks;
-  auto row_of = [&](int k) { return wave + kWaves * k; };
-  auto load_group = [&](int grp, float (&x)[kDepth][kChunks]) {
+  // D: rows I >= ja + k, so that J = I - k lies past the sinks.  A batch of
+  // rows that every lane of the wave sees (k0 .. k0 + 63) loads without a test.
+  const int k = t & (kDist - 1), grp = t / kDist;
+  const int k0 = __builtin_amdgcn_readfirstlane(k);
+  double d = 0.0;
+  // first batch that reaches row ja + k0
+  const int skip = max(0, ja + k0 - grp) / (kGroups * kDepth) * (kGroups * kDepth);
+  for (int i0 = grp + skip; i0 < nbw; i0 += kGroups * kDepth) {
+    float x[kDepth];
+    if (i0 - (k0 + 63) >= ja && i0 + (kDepth - 1) * kGroups < nbw) {
+      const float* p = e + (i0 * nb + (i0 - k));
 #pragma unroll
-    for (int d = 0; d < kDepth; ++d) {
-      const int I = row_of(grp * kDepth + d);
+      for (int u = 0; u < kDepth; ++u) x[u] = p[u * kGroups * (nb + 1)];
+    } else {
 #pragma unroll
-      for (int c = 0; c < kChunks; ++c) {
-        const int J = c * 64 + lane;
-        x[d][c] = (I < nb && J <= I) ? e[int64_t(I) * nb + J] : 0.0f;
+      for (int u = 0; u < kDepth; ++u) {
+        const int i = i0 + u * kGroups;
+        const bool in = i < nbw && i - k >= ja;
+        const float y = e[in ? i * nb + (i - k) : 0];
+        x[u] = in ? y : 0.0f;
       }
     }
-  };
-  auto process_row = [&](int I, const float (&x)[kChunks]) {
-    // prefix sums over J <= I of cols(J) * ebar[I][J]
-    double carry = 0.0;
 #pragma unroll
-    for (int c = 0; c < kChunks; ++c) {
-      if (c * 64 > I) break;
-      const int J = c * 64 + lane;
-      double v = static_cast<double>(x[c]) * static_cast<double>(min(kBlock, n - J * kBlock));
-      v = wave_inclusive_scan(v) + carry;
-      if (J <= I) {
-        pre[J] = v;
-        raw[J] = x[c];
-      }
+    for (int u = 0; u < kDepth; ++u) d += static_cast<double>(x[u]);
+  }
+  s_d[grp][k] = d;
+  if (grp == 0) {
+    s_line[0][k] = js + k < nbw ? e[int64_t(js + k) * nb + js] : 0.0f;
+    s_line[1][k] = (nbw < nb && nb - 1 - k >= ja) ? e[int64_t(nb - 1) * nb + (nb - 1 - k)] : 0.0f;
+  }
+  __syncthreads();
+  if (kGroups > 1 && grp == 0) {
+#pragma unroll
+    for (int v = 1; v < kGroups; ++v) d += s_d[v][k];
+    s_d[0][k] = d;
+  }
+  __syncthreads();
+
+  // Suffix sums: one wave per line, from the largest distance down.
+  if (wave < 3) {
+    double carry = 0.0;
+    s_suf[wave][kDist + lane] = 0.0;
+    for (int c = kDist - 64; c >= 0; c -= 64) {
+      const int kk = c + 63 - lane;
+      const double v = wave_inclusive_scan(wave == 0 ? s_d[0][kk] : static_cast<double>(s_line[wave - 1][kk])) + carry;
+      s_suf[wave][kk] = v;
       carry = lane63(v);
     }
-    if (!rule_ok) return;
-    const int r0 = I * kBlock;
-    const int rows = min(kBlock, n - r0);
-    // last completely masked block of this row block (band start of its first
-    // row; windows beyond the row cannot mask anything)
-    const int wc = min(w, (r0 >> a.band_shift) + 2);
-    const int bs0 = ((r0 >> a.band_shift) - wc + 1) * (1 << a.band_shift);
-    const int jb = min((bs0 >= 0 ? bs0 / kBlock : -((-bs0 + kBlock - 1) / kBlock)) - 1, I);
-    if (jb >= ja) {
-      const double lo = ja > 0 ? pre[ja - 1] : 0.0;
-      acc += static_cast<double>(rows) * (pre[jb] - lo);
-    }
-    // blocks masked in part: the block holding the sink edge, and with the
-    // token band the two blocks the band start sweeps across this row block
-    const int cand[3] = {js, a.band_shift ? -1 : jb + 1, a.band_shift ? -1 : jb + 2};
-#pragma unroll
-    for (int c = 0; c < 3; ++c) {
-      const int J = cand[c];
-      if (J < 0 || J > I || (J >= ja && J <= jb)) continue;
-      if (c > 0 && J == js) continue;
-      const int cnt = masked_in_block(I, J, n, s, w, a.band_shift);
-      acc += static_cast<double>(cnt) * static_cast<double>(raw[J]);
-    }
-  };
-  float cur[kDepth][kChunks], nxt[kDepth][kChunks];
-  load_group(0, cur);
-  for (int grp = 0; row_of(grp * kDepth) < nb; ++grp) {
-    load_group(grp + 1, nxt);
-#pragma unroll
-    for (int d = 0; d < kDepth; ++d) {
-      const int I = row_of(grp * kDepth + d);
-      if (I < nb) process_row(I, cur[d]);
-    }
-#pragma unroll
-    for (int d = 0; d < kDepth; ++d)
-#pragma unroll
-      for (int c = 0; c < kChunks; ++c) cur[d][c] = nxt[d][c];
   }
-  s_dl[wave][lane] = acc;
   __syncthreads();
-  if (wave != 0 || !rule_ok) return;
-  double dl = 0.0;
+
+  // Lane r of wave 0, 1, 2: rule r's share of D, C, L.
+  if (wave < 3 && lane < a.num_rules) {
+    const int w = a.window[lane];
+    const int k_full = bsh ? min(w, kDist) : min((w + 2 * kBlock - 2) / kBlock, kDist);
+    const int cols = wave == 1 ? kBlock - s % kBlock : kBlock;      // columns past the sinks
+    const int rows = wave == 2 ? rows_last : kBlock;
+    double acc = static_cast<double>(rows * cols) * s_suf[wave][k_full];
+    if (bsh == 0) {
 #pragma unroll
-  for (int v = 0; v < kWaves; ++v) dl += s_dl[v][lane];
-  a.dl[int64_t(h) * a.num_rules + lane] = dl;
+      for (int m = 1; m <= 2; ++m) {
+        const int kk = k_full - m;
+        if (kk < 0 || kk >= nb) continue;
+        // any whole block at distance kk stands for all of them
+        int cnt;
+        if (wave == 0) cnt = masked_in_block(ja + kk, ja, (ja + kk + 1) * kBlock, s, w, 0);
+        else if (wave == 1) cnt = masked_in_block(js + kk, js, (js + kk + 1) * kBlock, s, w, 0);
+        else cnt = nb - 1 - kk >= ja ? masked_in_block(nb - 1, nb - 1 - kk, n, s, w, 0) : 0;
+        acc += static_cast<double>(cnt) * (wave == 0 ? s_d[0][kk] : static_cast<double>(s_line[wave - 1][kk]));
+      }
+    }
+    if (wave == 2 && nbw < nb && js < nb)                            // where the two lines cross
+      acc += static_cast<double>(masked_in_block(nb - 1, js, n, s, w, bsh)) *
+             static_cast<double>(e[int64_t(nb - 1) * nb + js]);
+    s_part[wave][lane] = acc;
+  }
+  __syncthreads();
+  if (wave != 0 || lane >= a.num_rules) return;
+  a.dl[int64_t(h) * a.num_rules + lane] = s_part[0][lane] + (s_part[1][lane] + s_part[2][lane]);
   if (h == 0) a.density[lane] = static_cast<double>(a.kv_len[lane]) / static_cast<double>(n);
 }
 
 }  // namespace
 
+// Threads and rows in flight per work-group by the number of block rows; heads
+// x n: time before and now (54 rules, graph replays, three profiles in turn).
+//   nb <= 64: little to read, the start and the end of a work-group count:
+//     1024 x 2000: 12.7 -> 4.4 us (512 threads: 5.5).
+//   nb <= 256: 1024 x 8192: 44.0 -> 10.0 us (256 threads 10.7, 1024 12.4);
+//     128 x 16000: 71.6 -> 12.2 (18.7, 9.4); 1024 x 16000: 102.8 -> 37.4.
+//   above: one row at a time per work-group, so more of them in flight:
+//     32 x 32768: 190 -> 15.4 us (8 rows in flight 19.9, 512 threads 31.6);
+//     32 x 65536: 538 -> 56.8 (84.0 with 8 rows in flight).
 int launch_rule_loss(const RuleLossArgs& a, void* stream) {
   RuleLossArgs copy = a;
   void* args[] = {&copy};
   const void* kernel;
-  const int chunks = (a.nb + 63) / 64;
-  if (chunks <= 1) kernel = reinterpret_cast<const void*>(&rule_loss_kernel<1>);
-  else if (chunks <= 2) kernel = reinterpret_cast<const void*>(&rule_loss_kernel<2>);
-  else if (chunks <= 4) kernel = reinterpret_cast<const void*>(&rule_loss_kernel<4>);
-  else if (chunks <= 8) kernel = reinterpret_cast<const void*>(&rule_loss_kernel<8>);
-  else if (chunks <= 16) kernel = reinterpret_cast<const void*>(&rule_loss_kernel<16>);
-  else return static_cast<int>(hipErrorInvalidValue);
-  return static_cast<int>(hipLaunchKernel(kernel, dim3(static_cast<unsigned>(a.num_heads)), dim3(kWaves * 64), args,
-                                          0, static_cast<hipStream_t>(stream)));
+  unsigned threads = 512;
+  if (a.nb <= 64) {
+    kernel = reinterpret_cast<const void*>(&rule_loss_kernel<256, 64, 8>);
+    threads = 256;
+  } else if (a.nb <= 128) {
+    kernel = reinterpret_cast<const void*>(&rule_loss_kernel<512, 128, 8>);
+  } else if (a.nb <= 256) {
+    kernel = reinterpret_cast<const void*>(&rule_loss_kernel<512, 256, 8>);
+  } else if (a.nb <= 512) {
+    kernel = reinterpret_cast<const void*>(&rule_loss_kernel<1024, 512, 32>);
+    threads = 1024;
+  } else if (a.nb <= 1024) {
+    kernel = reinterpret_cast<const void*>(&rule_loss_kernel<1024, 1024, 32>);
+    threads = 1024;
+  } else {
+    return static_cast<int>(hipErrorInvalidValue);
+  }
+  return static_cast<int>(hipLaunchKernel(kernel, dim3(static_cast<unsigned>(a.num_heads)), dim3(threads), args, 0,
+                                          static_cast<hipStream_t>(stream)));
 }
 
 }  // namespace moa
