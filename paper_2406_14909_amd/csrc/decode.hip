@@ -10,8 +10,8 @@
 // Work split.  The caches differ in length by orders of magnitude across
 // heads, so the work is not cut per cache: all filled slots of the batch,
 // laid end to end in (sequence, KV head) order, form one virtual key range
-// that is cut into equal pieces, one per work-group ("worker"), with as many
-// workers as the chip holds resident work-groups.  A worker walks its piece
+// that is cut into equal pieces, one per work-group ("worker"), with at most
+// as many workers as the chip holds resident work-groups.  A worker walks its piece
 // cache by cache; its 4 waves take interleaved rows (or tiles) of each cache
 // and keep an online softmax (base 2, running max m, running sum l,
 // unnormalised output acc) for all G query heads of the KV head, so each K/V
@@ -82,31 +82,30 @@ constexpr int kWaves = 4;          // waves per worker (work-group)
 // tiles once K no longer came in operand layout from HBM.
 template <int G>
 constexpr int mma_keys() { return 32; }
-// Caches split over at most fast_parts<G>() workers merge in one pass: 32 for
-// GQA groups (their caches span up to about 24 workers), 16 otherwise.
-template <int G>
-constexpr int fast_parts() { return G >= 4 ? 32 : 16; }
 
-__device__ __forceinline__ int64_t worker_start(const DecodeArgs& a, int w) {
-  return int64_t(w) * a.per_worker + (int64_t(w) * a.rem) / a.workers;
+// a / b for 0 <= a < 2^53, b > 0 (the fp64 quotient is never below the floor;
+// a 64-bit integer division is a chain of several hundred cycles).
+__device__ __forceinline__ int64_t div_floor(int64_t a, int64_t b) {
+  const int64_t q = static_cast<int64_t>(static_cast<double>(a) / static_cast<double>(b));
+  return q * b > a ? q - 1 : q;
 }
 
-// The worker whose piece holds virtual key x (estimate, then exact correction).
-__device__ int worker_of(const DecodeArgs& a, int64_t x) {
-  int w = static_cast<int>(static_cast<double>(x) * static_cast<double>(a.workers) /
-                           static_cast<double>(a.total));
-  w = max(0, min(w, a.workers - 1));
-  while (w + 1 < a.workers && worker_start(a, w + 1) <= x) ++w;
-  while (w > 0 && worker_start(a, w) > x) --w;
-  return w;
+__device__ __forceinline__ int64_t uniform64(int64_t x) {
+  const uint32_t lo = __builtin_amdgcn_readfirstlane(static_cast<int>(x & 0xffffffff));
+  const uint32_t hi = __builtin_amdgcn_readfirstlane(static_cast<int>(x >> 32));
+  return static_cast<int64_t>((uint64_t(hi) << 32) | lo);
+}
+
+// The worker whose piece holds virtual key x.
+__device__ __forceinline__ int worker_of(const DecodeArgs& a, int64_t x) {
+  return __builtin_amdgcn_readfirstlane(static_cast<int>(div_floor(x, a.per_worker)));
 }
 
 // Filled slots of KV head g in sequence b; 0 for an idle sequence (negative
-// position).  Without per-sequence positions the virtual segment is the fill.
+// position).
 __device__ __forceinline__ int cache_fill(const DecodeArgs& a, int b, int g) {
-  if (a.positions == nullptr) return static_cast<int>(a.seg_start[g + 1] - a.seg_start[g]);
-  const int p = a.positions[b];
-  return p < 0 ? 0 : static_cast<int>(min(int64_t(p) + 1, int64_t(a.capacity[g])));
+  const int last = a.positions == nullptr ? a.last : a.positions[b];
+  return last < 0 ? 0 : min(last, a.capacity[g] - 1) + 1;
 }
 
 // Calls seg(b, g, lo, hi, whole) for each cache that worker w's piece touches:
@@ -114,18 +113,20 @@ __device__ __forceinline__ int cache_fill(const DecodeArgs& a, int b, int g) {
 // covers the cache's entire virtual segment.  Work-group uniform.
 template <class Seg>
 __device__ __forceinline__ void for_each_segment(const DecodeArgs& a, int w, Seg&& seg) {
-  int64_t x = worker_start(a, w);
-  const int64_t x_end = worker_start(a, w + 1);
+  int64_t x = int64_t(w) * a.per_worker;
+  const int64_t x_end = uniform64(min(a.total, x + a.per_worker));
   if (x >= x_end) return;
-  int b = static_cast<int>(x / a.seq_keys);
+  int b = __builtin_amdgcn_readfirstlane(static_cast<int>(div_floor(x, a.seq_keys)));
   int64_t r = x - int64_t(b) * a.seq_keys;
-  int g = 0;
-  while (a.seg_start[g + 1] <= r) ++g;
+  // All segment ends at once: a search entry by entry would be a chain of
+  // dependent reads of the kernel arguments.
+  const int lane = threadIdx.x & 63;
+  int g = __builtin_popcountll(__ballot(lane < a.hkv && a.seg_start[lane + 1] <= r));
   while (x < x_end) {
     const int64_t s0 = a.seg_start[g];
     const int len = static_cast<int>(a.seg_start[g + 1] - s0);
     const int lo = static_cast<int>(r - s0);
-    const int hi = static_cast<int>(min(int64_t(len), int64_t(lo) + (x_end - x)));
+    const int hi = __builtin_amdgcn_readfirstlane(static_cast<int>(min(int64_t(len), int64_t(lo) + (x_end - x))));
     seg(b, g, lo, hi, lo == 0 && hi == len);
     x += hi - lo;
     r += hi - lo;
@@ -201,13 +202,6 @@ __global__ void __launch_bounds__(kWaves * 64) decode_valu_kernel(DecodeArgs a) 
     const T* vbase = static_cast<const T*>(a.vc) + row0 * D + col * EPL;
 
     float qf[G][EPL];
-#pragma unroll
-    for (int h = 0; h < G; ++h) {
-      const Vec16<T> qv =
-          load16(static_cast<const T*>(a.q) + (int64_t(b) * a.hq + g * G + h) * D + col * EPL);
-#pragma unroll
-      for (int e = 0; e < EPL; ++e) qf[h][e] = qv.get(e) * a.scale_log2;
-    }
     float m[G], l[G], acc[G][EPL];
 #pragma unroll
     for (int h = 0; h < G; ++h) {
@@ -229,6 +223,17 @@ __global__ void __launch_bounds__(kWaves * 64) decode_valu_kernel(DecodeArgs a) 
         } else {
           kv[u] = zero16<T>();
           vv[u] = zero16<T>();
+        }
+      }
+      if (base == lo + wave * RPW) {
+        // The query comes after the first cache rows are on their way: its
+        // conversion would otherwise hold them back by one trip to memory.
+#pragma unroll
+        for (int h = 0; h < G; ++h) {
+          const Vec16<T> qv =
+              load16(static_cast<const T*>(a.q) + (int64_t(b) * a.hq + g * G + h) * D + col * EPL);
+#pragma unroll
+          for (int e = 0; e < EPL; ++e) qf[h][e] = qv.get(e) * a.scale_log2;
         }
       }
 #pragma unroll
@@ -534,8 +539,11 @@ __global__ void __launch_bounds__(kWaves * 64, mma_keys<G>() == 32 ? 3 : 2) deco
 // work-groups, each reading all the partials of every head.  The partials of
 // workers w0..w1 sit at consecutive slots w0 + cache .. w1 + cache.  Thread
 // groups of TPR threads (one float4 of each of the slice's head rows) take
-// every PG-th partial, so PG partial rows are read at once; the groups' sums
-// meet in LDS.
+// every PG-th partial, MD of them in flight, keep an online merge of their own
+// and meet in LDS.  All bound by latency: one trip for the partials.  The loads
+// are unconditional with the partial's number clamped: a branch per load, as an
+// earlier version had, makes a chain of them once the compiler knows the number
+// of partials to be uniform (10 us instead of 4).
 // ---------------------------------------------------------------------------
 template <int G>
 constexpr int merge_heads() { return G <= 2 ? G : 2; }   // query heads per merge work-group
@@ -547,11 +555,10 @@ __global__ void __launch_bounds__(256) decode_combine_kernel(DecodeArgs a) {
   constexpr int HS = merge_heads<G>();       // query heads per work-group
   constexpr int TPR = HS * V4;               // threads per partial (the slice's heads)
   constexpr int PG = 256 / TPR;              // partials read at once
-  constexpr int CH = 256;                    // partials whose weights are staged at a time
+  constexpr int MD = 4;                      // partials in flight per thread
   static_assert(TPR <= 256 && 256 % TPR == 0, "thread mapping");
-  __shared__ float s_w[HS][CH];
-  __shared__ float s_m[HS], s_inv[HS];
-  __shared__ f32x4 s_red[256];
+  __shared__ f32x4 s_acc[256];
+  __shared__ float s_m[256], s_l[256];
   const int bg = static_cast<int>(blockIdx.x) / (G / HS);
   const int h0 = (static_cast<int>(blockIdx.x) - bg * (G / HS)) * HS;   // first head of the slice
   const int b = bg / a.hkv, g = bg - b * a.hkv;
@@ -561,95 +568,56 @@ __global__ void __launch_bounds__(256) decode_combine_kernel(DecodeArgs a) {
   const int w0 = worker_of(a, base), w1 = worker_of(a, base + len - 1);
   if (w0 == w1) return;                       // written directly by its worker
   const int np = w1 - w0 + 1;
-  const float* part0 = a.part + (int64_t(w0) + bg) * G * PS;
-  auto at = [&](int p, int h) { return part0 + (int64_t(p) * G + h0 + h) * PS; };
-
-  constexpr int kFastParts = fast_parts<G>();
-  if (np <= kFastParts) {
-    // Few partials (the common case): every thread of the first TPR loads
-    // (m, l, its float4 of acc) of all of them at once and merges in one pass.
-    if (threadIdx.x >= TPR) return;
-    const int h = threadIdx.x / V4, d4 = threadIdx.x % V4;
-    float mp[kFastParts], lp[kFastParts];
-    f32x4 xp[kFastParts];
-#pragma unroll
-    for (int p = 0; p < kFastParts; ++p) {
-      if (p < np) {
-        const float* q = at(p, h);
-        mp[p] = q[D];
-        lp[p] = q[D + 1];
-        xp[p] = *reinterpret_cast<const f32x4*>(q + 4 * d4);
-      } else {
-        mp[p] = kNegBig;
-        lp[p] = 0.0f;
-        xp[p] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
-      }
-    }
-    float mx = kNegBig;
-#pragma unroll
-    for (int p = 0; p < kFastParts; ++p) mx = fmaxf(mx, mp[p]);
-    float ls = 0.0f;
-    f32x4 acc = {0.0f, 0.0f, 0.0f, 0.0f};
-#pragma unroll
-    for (int p = 0; p < kFastParts; ++p) {
-      const float wgt = fast_exp2(mp[p] - mx);
-      ls += wgt * lp[p];
-      acc += xp[p] * wgt;
-    }
-    acc *= 1.0f / ls;
-    T* op = static_cast<T*>(a.o) + (int64_t(b) * a.hq + g * G + h0 + h) * D + 4 * d4;
-#pragma unroll
-    for (int e = 0; e < 4; ++e) op[e] = static_cast<T>(acc[e]);
-    return;
-  }
-
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  for (int h = wave; h < HS; h += 4) {
-    float mx = kNegBig;
-    for (int p = lane; p < np; p += 64) mx = fmaxf(mx, at(p, h)[D]);
-#pragma unroll
-    for (int off = 32; off >= 1; off /= 2) mx = fmaxf(mx, __shfl_xor(mx, off, 64));
-    float ls = 0.0f;
-    for (int p = lane; p < np; p += 64) ls += fast_exp2(at(p, h)[D] - mx) * at(p, h)[D + 1];
-#pragma unroll
-    for (int off = 32; off >= 1; off /= 2) ls += __shfl_xor(ls, off, 64);
-    if (lane == 0) {
-      s_m[h] = mx;
-      s_inv[h] = 1.0f / ls;
-    }
-  }
-  __syncthreads();
-
-  const int pg = threadIdx.x / TPR, j = threadIdx.x % TPR;
+  const int pg = static_cast<int>(threadIdx.x) / TPR, j = static_cast<int>(threadIdx.x) % TPR;
   const int h = j / V4, d4 = j % V4;
+  const float* part0 = a.part + ((int64_t(w0) + bg) * G + h0 + h) * PS;
+  float m = kNegBig, l = 0.0f;
   f32x4 acc = {0.0f, 0.0f, 0.0f, 0.0f};
-  for (int p0 = 0; p0 < np; p0 += CH) {
-    const int nc = min(CH, np - p0);
-    for (int t = threadIdx.x; t < HS * CH; t += 256) {
-      const int hh = t / CH, c = t % CH;
-      s_w[hh][c] = c < nc ? fast_exp2(at(p0 + c, hh)[D] - s_m[hh]) : 0.0f;
-    }
-    __syncthreads();
-    const float* pp = at(p0, h) + 4 * d4;
-    const int64_t stride = int64_t(G) * PS;
-    int c = pg;
-    for (; c + 3 * PG < nc; c += 4 * PG) {
-      const f32x4 x0 = *reinterpret_cast<const f32x4*>(pp + (c + 0 * PG) * stride);
-      const f32x4 x1 = *reinterpret_cast<const f32x4*>(pp + (c + 1 * PG) * stride);
-      const f32x4 x2 = *reinterpret_cast<const f32x4*>(pp + (c + 2 * PG) * stride);
-      const f32x4 x3 = *reinterpret_cast<const f32x4*>(pp + (c + 3 * PG) * stride);
-      acc += x0 * s_w[h][c + 0 * PG] + x1 * s_w[h][c + 1 * PG];
-      acc += x2 * s_w[h][c + 2 * PG] + x3 * s_w[h][c + 3 * PG];
-    }
-    for (; c < nc; c += PG) acc += *reinterpret_cast<const f32x4*>(pp + c * stride) * s_w[h][c];
-    __syncthreads();
-  }
-  s_red[threadIdx.x] = acc;
-  __syncthreads();
-  if (pg != 0) return;
+  for (int p0 = pg; p0 < np; p0 += PG * MD) {
+    float mp[MD], lp[MD];
+    f32x4 xp[MD];
 #pragma unroll
-  for (int k = 1; k < PG; ++k) acc += s_red[k * TPR + j];
-  acc *= s_inv[h];
+    for (int u = 0; u < MD; ++u) {
+      const float* q = part0 + int64_t(min(p0 + u * PG, np - 1)) * G * PS;
+      mp[u] = q[D];
+      lp[u] = q[D + 1];
+      xp[u] = *reinterpret_cast<const f32x4*>(q + 4 * d4);
+    }
+    float mx = m;
+#pragma unroll
+    for (int u = 0; u < MD; ++u) mx = fmaxf(mx, mp[u]);
+    const float f = fast_exp2(m - mx);
+    l *= f;
+    acc *= f;
+    m = mx;
+#pragma unroll
+    for (int u = 0; u < MD; ++u) {
+      if (p0 + u * PG >= np) continue;
+      const float wgt = fast_exp2(mp[u] - mx);
+      l += wgt * lp[u];
+      acc += xp[u] * wgt;
+    }
+  }
+  if constexpr (PG > 1) {
+    s_acc[threadIdx.x] = acc;
+    s_m[threadIdx.x] = m;
+    s_l[threadIdx.x] = l;
+    __syncthreads();
+    if (pg != 0) return;
+    float mx = m;
+#pragma unroll
+    for (int v = 1; v < PG; ++v) mx = fmaxf(mx, s_m[v * TPR + j]);
+    const float f = fast_exp2(m - mx);
+    l *= f;
+    acc *= f;
+#pragma unroll
+    for (int v = 1; v < PG; ++v) {
+      const float wgt = fast_exp2(s_m[v * TPR + j] - mx);
+      l += wgt * s_l[v * TPR + j];
+      acc += s_acc[v * TPR + j] * wgt;
+    }
+  }
+  acc *= 1.0f / l;
   T* op = static_cast<T*>(a.o) + (int64_t(b) * a.hq + g * G + h0 + h) * D + 4 * d4;
 #pragma unroll
   for (int e = 0; e < 4; ++e) op[e] = static_cast<T>(acc[e]);
@@ -671,19 +639,52 @@ int resident_groups(const void* kernel, std::atomic<int>* cache) {
   return groups;
 }
 
+constexpr int64_t kMaxParts = 64;      // partials per cache in a call of short pieces
+constexpr int64_t kRoundedMax = 16;    // rounds per worker up to which pieces are whole rounds
+
 template <typename T, int D, int G>
 int launch_t(DecodeArgs a, void* stream) {
   constexpr bool kMma = sizeof(T) == 2 && G >= 2;
+  // Keys that a worker's waves read at once: one round of its loop.
+  constexpr int kRound = kMma ? kWaves * mma_keys<G>() : kWaves * 8 * (64 / (D / Vec16<T>::N));
   const void* kernel;
   if constexpr (kMma) kernel = reinterpret_cast<const void*>(&decode_mma_kernel<D, G>);
   else kernel = reinterpret_cast<const void*>(&decode_valu_kernel<T, D, G>);
   static std::atomic<int> group_cache[64];
-  int64_t workers = resident_groups(kernel, group_cache);
-  workers = std::min<int64_t>(workers, (a.total + kDecodeMinKeys - 1) / kDecodeMinKeys);
-  workers = std::max<int64_t>(1, std::min<int64_t>(workers, kMaxDecodeWorkers));
+  const int64_t slots = std::min<int64_t>(resident_groups(kernel, group_cache), kMaxDecodeWorkers);
+  // Short pieces are cut in whole rounds, each cache starting a new one: a
+  // piece of 257 keys where a round holds 128 takes three rounds, not two, and
+  // in a small call a round is a chain of about 3 us.  One round per worker is
+  // the fastest as long as the slots last and no cache has more than
+  // kMaxParts partials for the merge to read (per call: 32 heads of 1,064 keys
+  // on average 14.1 -> 8.1 us, of 2,112 keys 15.1 -> 12.5; 8 KV heads x 8 query
+  // heads of 2,112 keys 14.6 -> 9.9; 4 query heads, 8,256 keys, where the
+  // limit decides: 17.7 -> 15.7, without it 19.5).  From kRoundedMax rounds on
+  // the last, partial round weighs little and equal pieces fill the slots
+  // better.
+  int64_t rounds = 0, longest = 0;
+  for (int g = 0; g < a.hkv; ++g) {
+    const int64_t n = (a.seg_start[g + 1] - a.seg_start[g] + kRound - 1) / kRound;
+    rounds += n;
+    longest = std::max(longest, n);
+  }
+  const int64_t k = std::max((rounds * a.batch + slots - 1) / slots, (longest + kMaxParts - 1) / kMaxParts);
+  if (k <= kRoundedMax) {
+    int64_t at = 0, prev = 0;
+    for (int g = 0; g < a.hkv; ++g) {
+      const int64_t end = a.seg_start[g + 1];
+      at += (end - prev + kRound - 1) / kRound * kRound;
+      prev = end;
+      a.seg_start[g + 1] = at;
+    }
+    a.seq_keys = at;
+    a.total = at * a.batch;
+    a.per_worker = k * kRound;
+  } else {
+    a.per_worker = (a.total + slots - 1) / slots;
+  }
+  const int64_t workers = (a.total + a.per_worker - 1) / a.per_worker;
   a.workers = static_cast<int32_t>(workers);
-  a.per_worker = a.total / workers;
-  a.rem = static_cast<int32_t>(a.total % workers);
   void* args[] = {&a};
   hipError_t e = hipLaunchKernel(kernel, dim3(static_cast<unsigned>(workers)), dim3(kWaves * 64), args, 0,
                                  static_cast<hipStream_t>(stream));

@@ -333,6 +333,7 @@ moa_status_t moa_decode(const moa_plan_t* plan, const void* q, const void* k_cac
   DecodeArgs a;
   const moa_status_t st = decode_args(*plan, "moa_decode", q, k_cache, v_cache, o, batch, workspace, seg_len, &a);
   if (st != MOA_OK) return st;
+  a.last = static_cast<int32_t>(pos);
   const int err = launch_decode(a, d.dtype, d.head_dim, plan->group, hip_stream);
   if (err) return fail(MOA_ERR_HIP, "moa_decode: kernel launch failed (hipError " + std::to_string(err) + ")");
   return ok();
@@ -365,6 +366,7 @@ moa_status_t moa_decode_noalloc(const moa_plan_t* plan, const void* q, const voi
   DecodeArgs a;
   const moa_status_t st = decode_args(*plan, "moa_decode_noalloc", q, k_cache, v_cache, o, batch, ws, seg_len, &a);
   if (st != MOA_OK) return st;
+  a.last = static_cast<int32_t>(pos);
   const int err = launch_decode(a, d.dtype, d.head_dim, plan->group, hip_stream);
   if (err) return fail(MOA_ERR_HIP, "moa_decode_noalloc: kernel launch failed (hipError " + std::to_string(err) + ")");
   return ok();

@@ -73,9 +73,8 @@ struct AppendArgs {
 
 // Decode work split: the filled cache slots of every (sequence, KV head) pair,
 // laid end to end in (sequence, head) order, form one virtual key range of
-// `total` keys, cut into `workers` near-equal pieces (one per wave):
-// worker w covers [start(w), start(w + 1)) with
-// start(w) = w * per_worker + (w * rem) / workers.  Head g of a sequence owns
+// `total` keys, cut into equal pieces (one per work-group): worker w covers
+// [w * per_worker, (w + 1) * per_worker).  Head g of a sequence owns
 // virtual keys [seg_start[g], seg_start[g + 1]) of that sequence's range.
 struct DecodeArgs {
   const void* q;
@@ -85,11 +84,11 @@ struct DecodeArgs {
   float* part;               // [workers + batch * hkv][group][head_dim + 4] partials
   const int32_t* positions;  // per-sequence positions (device), or null: one position for all
   int64_t rows_total;        // cache rows per sequence
-  int64_t total;             // virtual keys = batch * seq_keys
+  int64_t total;             // virtual keys = batch * seq_keys (the launcher may round each head's up)
   int64_t seq_keys;          // virtual keys per sequence (= seg_start[hkv])
-  int64_t per_worker;        // total / workers (set by the launcher)
-  int32_t rem;               // total % workers (set by the launcher)
+  int64_t per_worker;        // ceil(total / workers) (set by the launcher)
   int32_t workers;           // set by the launcher
+  int32_t last;              // position of every sequence, where positions is null
   int32_t batch;
   int32_t hq;
   int32_t hkv;
@@ -148,7 +147,6 @@ constexpr int kPrefillUnitBlocks = 64;  // minimum work-groups per prefill dispa
 constexpr int kNumXcd = 8;          // accelerator dies; work-groups go round-robin over them
 constexpr int64_t kLastLevelCacheBytes = int64_t(256) << 20;   // MI355X Infinity Cache
 constexpr int kMaxDecodeWorkers = 8192;  // decode workers (waves) per launch, at most
-constexpr int kDecodeMinKeys = 256;      // virtual keys per decode worker, at least
 constexpr int kDecodePartPad = 4;        // partial row: head_dim sums, m, l, 2 pad floats
 constexpr size_t kDecodeScratchBytes = MOA_DECODE_SCRATCH_BYTES;   // library-owned decode workspace per GPU
 constexpr int kInfluenceBlock = 64;      // profiling block (tokens)
