@@ -4,6 +4,11 @@ Argument marshalling only: shapes and dtypes of torch tensors are checked and
 their device pointers, together with torch's current HIP stream, are handed to
 the library.  Every step of the computation runs in the library's kernels;
 there is no fallback.  If libmoa.so is missing, loading fails with an error.
+
+A call on plain tensors of the current device and stream is checked and made by
+the native module _binding (step append + decode: 31 us of host time before,
+10 us now); it leaves every other call, and every call that it or the library
+refuses, to the code here, which says what is wrong with it.
 """
 from __future__ import annotations
 
@@ -53,13 +58,20 @@ class MoaError(RuntimeError):
         self.status = status
 
 
+# Entry points that the native call path takes, in the order of its table.
+_NATIVE = ("moa_prefill", "moa_kv_append", "moa_decode", "moa_decode_noalloc", "moa_kv_append_ragged",
+           "moa_decode_ragged", "moa_influence", "moa_rule_loss")
+
 _lib = None
+_fast = None        # the native call path (_binding), loaded with the library
+_table = None       # addresses of _NATIVE in the loaded library
+_bound = None       # its calls that take no plan
 
 
 def load_library(path: Optional[str] = None) -> ctypes.CDLL:
     """Loads libmoa.so once.  torch is imported first so that the library
     binds to the same HIP runtime instance as torch (same soname)."""
-    global _lib
+    global _lib, _fast, _table, _bound
     if _lib is not None:
         return _lib
     import torch  # noqa: F401  (shares its HIP runtime with the library)
@@ -97,6 +109,10 @@ def load_library(path: Optional[str] = None) -> ctypes.CDLL:
     lib.moa_rule_loss.restype = ctypes.c_int
     lib.moa_last_error.argtypes = []
     lib.moa_last_error.restype = ctypes.c_char_p
+    from . import _binding
+    _fast = _binding
+    _table = tuple(ctypes.cast(getattr(lib, name), vp).value for name in _NATIVE)
+    _bound = _binding.bind(_table, 0, 0, 0, 0, 0, True)
     _lib = lib
     return lib
 
@@ -118,6 +134,8 @@ class Plan:
         self.offset = np.zeros(hkv + 1, dtype=np.int64)
         _check(load_library().moa_plan_tables(self.handle, self.window.ctypes.data,
                                               self.capacity.ctypes.data, self.offset.ctypes.data))
+        self._bound = _fast.bind(_table, handle, desc.num_q_heads, hkv, desc.head_dim, self.cache_rows,
+                                 desc.dtype == MOA_BF16)
 
     @property
     def num_q_heads(self) -> int:
@@ -145,6 +163,7 @@ class Plan:
         return torch.bfloat16 if self.desc.dtype == MOA_BF16 else torch.float32
 
     def free(self) -> None:
+        self._bound = None
         if self.handle is not None and self.handle.value:
             load_library().moa_plan_free(self.handle)
             self.handle = None
@@ -206,6 +225,10 @@ def _need(t, shape, dtype, name):
 
 def moa_prefill(plan: Plan, q, k, v, o=None, stream=None):
     """o[b,i,h,:] = MoA attention of q over k, v ([B, n, H, D] layouts)."""
+    if stream is None:
+        done = _fast.prefill(plan._bound, q, k, v, o)
+        if done is not None:
+            return done
     import torch
     bsz, n = int(q.shape[0]), int(q.shape[1])
     dt = plan.torch_dtype
@@ -234,6 +257,8 @@ def new_cache(plan: Plan, batch: int, device="cuda"):
 def moa_kv_append(plan: Plan, k_cache, v_cache, pos_cache, k_new, v_new, start_pos: int,
                   stream=None) -> None:
     """Appends positions start_pos .. start_pos + n_new - 1 (k_new: [B, n_new, H_kv, D])."""
+    if stream is None and _fast.kv_append(plan._bound, k_cache, v_cache, pos_cache, k_new, v_new, start_pos):
+        return
     import torch
     bsz, n_new = int(k_new.shape[0]), int(k_new.shape[1])
     dt = plan.torch_dtype
@@ -261,6 +286,10 @@ def new_workspace(plan: Plan, batch: int, device="cuda"):
 
 def moa_decode(plan: Plan, q, k_cache, v_cache, pos: int, workspace, o=None, stream=None):
     """Decode output for the token at `pos` (q, o: [B, H_q, D])."""
+    if stream is None:
+        done = _fast.decode(plan._bound, q, k_cache, v_cache, pos, workspace, o)
+        if done is not None:
+            return done
     import torch
     bsz = int(q.shape[0])
     dt = plan.torch_dtype
@@ -288,6 +317,10 @@ def moa_decode_noalloc(plan: Plan, q, k_cache, v_cache, pos: int, o, stream=None
     partials in its own fixed per-GPU array (MOA_DECODE_SCRATCH_BYTES), so the
     call allocates nothing; o must be given (q, o: [B, H_q, D]).  Calls that
     overlap in time on one GPU share that array and race."""
+    if stream is None:
+        done = _fast.decode_noalloc(plan._bound, q, k_cache, v_cache, pos, o)
+        if done is not None:
+            return done
     bsz = int(q.shape[0])
     dt = plan.torch_dtype
     _need(q, (bsz, plan.num_q_heads, plan.head_dim), dt, "q")
@@ -313,6 +346,8 @@ def _positions(positions, bsz):
 def moa_kv_append_ragged(plan: Plan, k_cache, v_cache, pos_cache, k_new, v_new, positions,
                          stream=None) -> None:
     """One token per sequence at its own position (k_new: [B, 1, H_kv, D]; positions: int32[B])."""
+    if stream is None and _fast.kv_append_ragged(plan._bound, k_cache, v_cache, pos_cache, k_new, v_new, positions):
+        return
     import torch
     bsz = int(k_new.shape[0])
     dt = plan.torch_dtype
@@ -330,6 +365,10 @@ def moa_kv_append_ragged(plan: Plan, k_cache, v_cache, pos_cache, k_new, v_new, 
 
 def moa_decode_ragged(plan: Plan, q, k_cache, v_cache, positions, workspace, o=None, stream=None):
     """Decode with sequence b at position positions[b] (q, o: [B, H_q, D])."""
+    if stream is None:
+        done = _fast.decode_ragged(plan._bound, q, k_cache, v_cache, positions, workspace, o)
+        if done is not None:
+            return done
     import torch
     bsz = int(q.shape[0])
     dt = plan.torch_dtype
@@ -355,6 +394,11 @@ def moa_influence(q, k, v, dout, ebar=None, softmax_scale: float = 0.0, stream=N
     attention over a batch of calibration items (paper Sec. 3.3, Eq. 3).
 
     q, dout: [B, n, H_q, D] bf16; k, v: [B, n, H_kv, D] bf16 (GPU, contiguous)."""
+    if stream is None:
+        load_library()
+        done = _fast.influence(_bound, q, k, v, dout, ebar, softmax_scale)
+        if done is not None:
+            return done
     import torch
     bsz, n, hq, d = (int(x) for x in q.shape)
     hkv = int(k.shape[2])
@@ -376,6 +420,11 @@ def moa_rule_loss(ebar, n: int, num_sink: int, alpha, beta, flags: int = 0, stre
     """(dl [H, R] fp64, density [R] fp64) on the GPU: the loss of every candidate
     rule for every head at length n (paper Sec. 3.3, Eq. 4) from the
     block-averaged influence ebar [H, nb, nb] (fp32, GPU)."""
+    if stream is None:
+        load_library()
+        done = _fast.rule_loss(_bound, ebar, n, num_sink, alpha, beta, flags)
+        if done is not None:
+            return done
     import torch
     h = int(ebar.shape[0])
     nb = -(-int(n) // 64)

@@ -1,0 +1,99 @@
+"""The native call path of the Python binding against its general path: the same
+results, the same refusals, and the general path wherever a call is out of the
+ordinary."""
+import numpy as np
+import pytest
+import torch
+
+from paper_2406_14909_amd import moa as M
+from paper_2406_14909_amd import search
+
+pytestmark = pytest.mark.gpu
+
+
+def _state(dt="bf16", b=2, n=150, hq=4, hkv=2, d=64):
+    plan = M.moa_plan(hq, hkv, d, 4, n, dt, [30.0, 100.0], [0.0, 0.0])
+    gen = torch.Generator(device="cuda").manual_seed(5)
+    draw = lambda *shape: torch.randn(shape, generator=gen, device="cuda").to(plan.torch_dtype)
+    return plan, draw(b, n, hq, d), draw(b, n, hkv, d), draw(b, n, hkv, d)
+
+
+def _whole_path(stream, dt):
+    """Every entry point once; stream None takes the native path, a stream the general one."""
+    plan, q, k, v = _state(dt)
+    b, n = q.shape[:2]
+    out = [M.moa_prefill(plan, q, k, v, stream=stream)]
+    kc, vc, pc = M.new_cache(plan, b)
+    ws = M.new_workspace(plan, b)
+    M.moa_kv_append(plan, kc, vc, pc, k, v, 0, stream=stream)
+    last = [x[:, -1:].contiguous() for x in (k, v)]
+    M.moa_kv_append(plan, kc, vc, pc, *last, n, stream=stream)
+    qd = q[:, -1].contiguous()
+    out += [kc.clone(), vc.clone(), pc.clone(), M.moa_decode(plan, qd, kc, vc, n, ws, stream=stream)]
+    out.append(M.moa_decode_noalloc(plan, qd, kc, vc, n, torch.empty_like(qd), stream=stream))
+    at = torch.tensor([n + 1, -1], dtype=torch.int32, device="cuda")
+    M.moa_kv_append_ragged(plan, kc, vc, pc, *last, at, stream=stream)
+    out += [kc, vc, pc, M.moa_decode_ragged(plan, qd, kc, vc, at, ws, o=torch.zeros_like(qd), stream=stream)]
+    if dt == "bf16":
+        e = M.moa_influence(q, k, v, q.flip(1).contiguous(), stream=stream)
+        out += [e, *M.moa_rule_loss(e, n, 4, *search.candidate_rules(), stream=stream)]
+    return out
+
+
+@pytest.mark.parametrize("dt", ["bf16", "f32"])
+def test_native_path_equals_general_path(dt):
+    print("[case] binding", dt, flush=True)
+    for a, b in zip(_whole_path(None, dt), _whole_path(torch.cuda.current_stream(), dt)):
+        assert a.dtype == b.dtype and torch.equal(a, b)
+
+
+def test_native_path_takes_ordinary_calls_and_leaves_the_others():
+    print("[case] binding routes", flush=True)
+    plan, q, k, v = _state()
+    native = lambda *a: M._fast.prefill(plan._bound, *a)
+    o = torch.empty_like(q)
+    assert native(q, k, v, o) is o and native(q, k, v, None).shape == q.shape
+    odd = [(q[:, :-1], k, v, None), (q, k.float(), v, None), (q, k, v.cpu(), None), (q, k, v, o[:1]),
+           (q.transpose(0, 1).contiguous().transpose(0, 1), k, v, None), (q.reshape(-1), k, v, None), (None, k, v, None)]
+    for a in odd:
+        assert native(*a) is None
+    with torch.device("cpu"):                      # an active torch function mode
+        assert native(q, k, v, o) is None
+        M.moa_prefill(plan, q, k, v, o)
+    assert torch.vmap(lambda x: x * (native(x, k, v, None) is None))(q[None]).equal(q[None])
+    with pytest.raises(M.MoaError, match="expected dtype"):
+        M.moa_prefill(plan, q, k.float(), v)
+    with pytest.raises(M.MoaError, match="overlaps"):
+        M.moa_prefill(plan, q, k, v, q)
+    kc, vc, pc = M.new_cache(plan, 2)
+    M.moa_kv_append(plan, kc, vc, pc, k, v, np.int64(0))        # any integer is a position
+    with pytest.raises(M.MoaError, match="start_pos"):
+        M.moa_kv_append(plan, kc, vc, pc, k, v, -1)
+    with pytest.raises(M.MoaError, match="workspace"):
+        M.moa_decode(plan, q[:, 0].contiguous(), kc, vc, 10, torch.empty(256, dtype=torch.uint8, device="cuda"))
+    e = torch.zeros((2, 3, 3), device="cuda")
+    assert M.moa_rule_loss(e, 150, 4, [1.0, 2.0], [0.0, 0.0])[0].shape == (2, 2)     # lists, as before
+    with pytest.raises(M.MoaError, match="1-D"):
+        M.moa_rule_loss(e, 150, 4, np.zeros(2), np.zeros(3))
+    bound = plan._bound
+    plan.free()
+    assert bound is not None and plan._bound is None and M._fast.prefill(plan._bound, q, k, v, o) is None
+
+
+def test_native_path_runs_on_the_current_stream():
+    print("[case] binding stream", flush=True)
+    plan, q, k, v = _state()
+    ref = M.moa_prefill(plan, q, k, v)
+    side = torch.cuda.Stream()
+    side.wait_stream(torch.cuda.current_stream())
+    g = torch.cuda.CUDAGraph()
+    with torch.cuda.stream(side):
+        o = M.moa_prefill(plan, q, k, v)
+        side.synchronize()
+        with torch.cuda.graph(g, stream=side):     # captured, so it ran on this stream
+            p = M.moa_prefill(plan, q, k, v)
+    p.zero_()
+    torch.cuda.synchronize()
+    g.replay()
+    torch.cuda.synchronize()
+    assert torch.equal(o, ref) and torch.equal(p, ref)
