@@ -25,7 +25,7 @@ BINDING_PATH = os.path.join(PKG_DIR, "_binding.so")
 # matrix-core ceilings of the GPU.
 PROBES = ["stream_read", "mfma_loop"]
 
-HIP_SOURCES = ["kv_append.hip", "decode.hip", "prefill.hip", "influence.hip", "rule_loss.hip"]
+HIP_SOURCES = ["kv_append.hip", "decode.hip", "prefill.hip", "prefill_f32.hip", "influence.hip", "rule_loss.hip"]
 HOST_SOURCES = ["moa_api.cpp"]
 
 ARCH = "gfx950"

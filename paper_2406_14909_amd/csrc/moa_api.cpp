@@ -209,10 +209,6 @@ moa_status_t moa_prefill(const moa_plan_t* plan, const void* q, const void* k, c
   a.hkv = d.num_kv_heads;
   a.group = plan->group;
   a.num_sink = d.num_sink;
-  a.n_qtiles = static_cast<int32_t>(tiles);
-  a.qchunk = static_cast<int32_t>(qchunk);
-  a.n_chunks = static_cast<int32_t>(n_chunks);
-  a.n_units = static_cast<int32_t>(n_units);
   a.scale_log2 = plan->scale * 1.4426950408889634f;
   a.band_shift = (d.flags & MOA_BLOCK_BAND) ? 6 : 0;
   static_assert(MOA_BAND_BLOCK == 64, "band_shift is log2(MOA_BAND_BLOCK)");
@@ -225,7 +221,8 @@ moa_status_t moa_prefill(const moa_plan_t* plan, const void* q, const void* k, c
                                              : plan->window[h];
     a.kv_order[h] = plan->kv_order[h];
   }
-  const int err = launch_prefill(a, d.dtype, d.head_dim, hip_stream);
+  const int err = d.dtype == MOA_BF16 ? launch_prefill(a, d.head_dim, hip_stream)
+                                      : launch_prefill_f32(a, d.head_dim, hip_stream);
   if (err) return fail(MOA_ERR_HIP, "moa_prefill: kernel launch failed (hipError " + std::to_string(err) + ")");
   return ok();
 }

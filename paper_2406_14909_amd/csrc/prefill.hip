@@ -8,23 +8,22 @@
 // One work-group = 4 waves = 128 query rows of one (sequence, query head);
 // each wave owns 32 rows.  The work-group walks only the 64-key tiles that
 // intersect the sink prefix or the band of its rows; every other tile is
-// skipped without being read.  K and V tiles are staged in LDS (double
-// buffered: the global loads of tile t+1 are in flight while tile t is
-// computed, one barrier per tile) and shared by the 4 waves.
+// skipped without being read.  K and V tiles are staged in LDS (the global
+// loads of the next tiles are in flight while a tile is computed, one barrier
+// per tile) and shared by the 4 waves.  fp32 plans have a kernel of their own.
 //
-// Matrix-core formulation (CDNA4 32x32 MFMA; bf16 32x32x16, fp32 32x32x2):
+// Matrix-core formulation (CDNA4 32x32x16 bf16 MFMA):
 //   S^T = K Q^T  : A = K tile rows (keys), B = Q^T kept in registers.
 //                  Output lane l holds the scores of query row l % 32 for
 //                  16 keys, so the row softmax needs one cross-lane step.
 //   O^T += V^T P^T : B = P^T taken straight from the score registers
-//                  (converted to the input type), A = V^T.  For bf16 the V
-//                  tile stays row-major in LDS and the transposing LDS read
-//                  (ds_read_b64_tr_b16) delivers V^T fragments; the fp32
-//                  instantiation stores V transposed instead.
+//                  (converted to bf16), A = V^T.  The V tile stays row-major in
+//                  LDS and the transposing LDS read (ds_read_b64_tr_b16)
+//                  delivers V^T fragments.
 // The key order inside each 16-key MFMA step is permuted identically on both
 // operands, which leaves the sum unchanged.
-// Softmax is online in base 2 with the scale folded into one FMA per score
-// (bf16 instantiation); the row sum is accumulated over the bf16-rounded
+// Softmax is online in base 2 with the scale folded into one FMA per score;
+// the row sum is accumulated over the bf16-rounded
 // probabilities that the PV product uses.
 // The running maximum used as the exponent offset is raised only when some
 // row of the wave would otherwise see exponents above 2^8 (a wave-uniform
@@ -32,43 +31,27 @@
 // normalisation by the running sum makes the result independent of that
 // offset.  The mask is evaluated only on tiles that are not entirely visible
 // to the wave's rows.
+#include <algorithm>
+
 #include "moa_device.h"
 
 namespace moa {
 
 namespace {
 
-constexpr int BM = 128;   // query rows per work-group
 constexpr int BN = 64;    // keys per tile
-constexpr int NW = 4;     // waves per work-group
 constexpr float kRescaleSlack = 8.0f;   // log2 headroom before the offset is raised
 
 typedef short i16x4 __attribute__((ext_vector_type(4)));
 
-template <typename T> struct Mma;
-
-template <> struct Mma<bf16> {
-  static constexpr int K = 16;                 // reduction depth per instruction
-  typedef bf16x8 frag;
-  __device__ __forceinline__ static f32x16 mma(const frag& a, const frag& b, const f32x16& c) {
-    return __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, b, c, 0, 0, 0);
-  }
-};
-
-template <> struct Mma<float> {
-  static constexpr int K = 2;
-  typedef float frag;
-  __device__ __forceinline__ static f32x16 mma(const frag& a, const frag& b, const f32x16& c) {
-    return __builtin_amdgcn_mfma_f32_32x32x2f32(a, b, c, 0, 0, 0);
-  }
-};
-
-// Fragment of K / Q for reduction step kk: elements kk*K + half*(K/2) ... (+K/2).
-__device__ __forceinline__ bf16x8 load_frag(const bf16* base, int kk, int half) {
-  return *reinterpret_cast<const bf16x8*>(base + kk * 16 + half * 8);
-}
-__device__ __forceinline__ float load_frag(const float* base, int kk, int half) {
-  return base[kk * 2 + half];
+__device__ __forceinline__ f32x16 mma(const bf16x8& a, const bf16x8& b, const f32x16& c) {
+#if defined(__HIP_DEVICE_COMPILE__)
+  return __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, b, c, 0, 0, 0);
+#else
+  (void)a;
+  (void)b;
+  return c;
+#endif
 }
 
 // Transposing LDS read of four bf16: within each 16-lane group, lane 4a+b
@@ -98,47 +81,42 @@ __device__ __forceinline__ float dot2_ones(bf16 a, bf16 b, float acc) {
 #endif
 }
 
-// x * y - z with the product rounded on its own (never fused).
-__device__ __forceinline__ float mul_then_sub(float x, float y, float z) {
-#pragma clang fp contract(off)
-  return x * y - z;
-}
-
-template <typename T, int D>
+// NR waves of 32 query rows stage one key group's tiles.
+template <int D, int NR>
 struct Tiles {
-  static constexpr bool kTr = sizeof(T) == 2;        // bf16: V via the transposing read
-  static constexpr int RB = D * int(sizeof(T));      // bytes per K/V row
+  static constexpr int RB = D * 2;                   // bytes per K/V row
   static constexpr int CPR = RB / 16;                // 16-byte chunks per row
-  static constexpr int TILE_BYTES = BN * RB;         // one K (or bf16 V) tile, rows unpadded
-  static constexpr int DMA_PER_WAVE = TILE_BYTES / 1024 / NW;   // 1 KB direct-to-LDS loads
-  // K stages in LDS: bf16 keeps K two tiles ahead (3 buffers, 80 KB per
-  // work-group with V); the fp32 instantiation keeps one tile ahead.
-  static constexpr int KSTAGES = kTr ? 3 : 2;
-  static constexpr int EPL = Vec16<T>::N;            // elements per 16-byte chunk
-  static constexpr int VT_LD = BN + 4;               // fp32 only: V^T row stride (elements)
-  static constexpr int VT_BYTES = D * VT_LD * int(sizeof(T));
-  static constexpr int V_BYTES = kTr ? TILE_BYTES : VT_BYTES;
-  static constexpr int VREG = kTr ? 1 : BN * CPR / (NW * 64);   // fp32 V chunks staged per thread
+  static constexpr int TILE_BYTES = BN * RB;         // one K or V tile, rows unpadded
+  static constexpr int DMA_PER_WAVE = TILE_BYTES / 1024 / NR;   // 1 KB direct-to-LDS loads
+  // K is kept two tiles ahead (3 buffers), V one (2): 80 KB at head_dim 128.
+  static constexpr int KSTAGES = 3;
   // K rows: chunk c of row r sits at chunk position c ^ swz_k(r), so the 16
   // rows read together by an MFMA operand load hit 16 different bank groups.
   __device__ __forceinline__ static int swz_k(int r) { return CPR >= 16 ? (r & 15) : ((r >> 1) & 7); }
-  // V rows (bf16): depends on r mod 8 only; the 4 rows x 4 chunks read by half
-  // a wave in one transposing load hit 16 different bank groups.
+  // V rows: depends on r mod 8 only; the 4 rows x 4 chunks read by half a wave
+  // in one transposing load hit 16 different bank groups.
   __device__ __forceinline__ static int swz_v(int r) { return CPR >= 16 ? 4 * (r & 3) : 4 * ((r >> 1) & 1); }
 };
 
-template <typename T, int D>
-__global__ void __launch_bounds__(NW * 64, 2) prefill_kernel(PrefillArgs a) {
-  using M = Mma<T>;
-  using TL = Tiles<T, D>;
-  constexpr int KS = D / M::K;            // MFMA steps over the head dimension
-  constexpr int RB = TL::RB, CPR = TL::CPR, EPL = TL::EPL, KST = TL::KSTAGES;
+// KG key groups of NR waves share the 32 * NR query rows: group kg takes tiles
+// kg, kg + KG, ... through LDS stages of its own, and the groups' states meet in
+// LDS at the end.
+template <int D, int NR, int KG>
+__global__ void __launch_bounds__(NR * KG * 64, 2) prefill_kernel(PrefillArgs a) {
+  using TL = Tiles<D, NR>;
+  constexpr int BM = 32 * NR;             // query rows per work-group
+  constexpr int KS = D / 16;              // MFMA steps over the head dimension
+  constexpr int RB = TL::RB, CPR = TL::CPR, KST = TL::KSTAGES;
 
-  __shared__ __attribute__((aligned(1024))) char sK[KST][TL::TILE_BYTES];
-  __shared__ __attribute__((aligned(1024))) char sV[2][TL::V_BYTES];
+  constexpr int kGroupBytes = (KST + 2) * TL::TILE_BYTES;
+  __shared__ __attribute__((aligned(1024))) char s_tiles[KG * kGroupBytes];
 
   const int lane = threadIdx.x & 63;
-  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);   // wave-uniform (scalar)
+  const int wave_id = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);   // wave-uniform (scalar)
+  const int wave = KG == 1 ? wave_id : wave_id % NR;                    // of the key group: rows
+  const int kg = KG == 1 ? 0 : wave_id / NR;
+  char* const sK = s_tiles + kg * kGroupBytes;
+  char* const sV = sK + KST * TL::TILE_BYTES;
   const int lrow = lane & 31;
   const int half = lane >> 5;
 
@@ -187,35 +165,33 @@ __global__ void __launch_bounds__(NW * 64, 2) prefill_kernel(PrefillArgs a) {
 
   const int64_t q_row_stride = int64_t(a.hq) * D;
   const int64_t kv_row_bytes = int64_t(a.hkv) * RB;
-  const T* qg = static_cast<const T*>(a.q) + (int64_t(b) * n * a.hq + h) * D;
-  const char* kg = static_cast<const char*>(a.k) + (int64_t(b) * n * a.hkv + g) * RB;
-  const char* vg = static_cast<const char*>(a.v) + (int64_t(b) * n * a.hkv + g) * RB;
+  const bf16* qg = static_cast<const bf16*>(a.q) + (int64_t(b) * n * a.hq + h) * D;
+  const char* k_base = static_cast<const char*>(a.k) + (int64_t(b) * n * a.hkv + g) * RB;
+  const char* v_base = static_cast<const char*>(a.v) + (int64_t(b) * n * a.hkv + g) * RB;
 
   // Q^T fragments of this lane's query row (loaded after the first tiles' DMA
   // is issued, see the pipeline prologue).
-  typename M::frag qf[KS];
+  bf16x8 qf[KS];
 
   // Direct-to-LDS tile loads: DMA instruction I writes buffer bytes
   // [I*1024, I*1024 + 1024) and lane L's 16 bytes land at chunk I*64 + L.
-  // K: chunk m is row m / (CPR+1), column chunk m % (CPR+1); the last column
-  // chunk of each row (and anything past the tile) is padding and re-reads the
-  // row's first chunk.  V (bf16): chunk I*64 + L is row r, position p, and
-  // carries global chunk p ^ swz_v(r).  Keys past the end re-read the last key
-  // (always masked by causality).
+  // Chunk m is row m / CPR, position p = m % CPR, and carries global chunk
+  // p ^ swz(row).  Keys past the end re-read the last key (always masked by
+  // causality).
   // Per-lane byte offsets of the DMA sources relative to the tile's first key
   // row (tile independent).  DMA instruction I writes tile bytes
   // [I*1024, I*1024 + 1024): lane L's 16 bytes land at chunk m = I*64 + L, i.e.
   // row m / CPR, chunk position m % CPR, and carry global chunk
   // position ^ swz(row).  Wave w issues instructions w*DMA_PER_WAVE + i.
   constexpr int DPW = TL::DMA_PER_WAVE;
-  uint32_t k_src[DPW], v_src[TL::kTr ? DPW : 1];
+  uint32_t k_src[DPW], v_src[DPW];
   auto dma_row = [&](int i) { return ((wave * DPW + i) * 64 + lane) / CPR; };
 #pragma unroll
   for (int i = 0; i < DPW; ++i) {
     const int m = (wave * DPW + i) * 64 + lane;
     const int r = m / CPR, p = m % CPR;
     k_src[i] = uint32_t(r) * uint32_t(kv_row_bytes) + uint32_t(p ^ TL::swz_k(r)) * 16u;
-    if constexpr (TL::kTr) v_src[i] = uint32_t(r) * uint32_t(kv_row_bytes) + uint32_t(p ^ TL::swz_v(r)) * 16u;
+    v_src[i] = uint32_t(r) * uint32_t(kv_row_bytes) + uint32_t(p ^ TL::swz_v(r)) * 16u;
   }
   // With a.rotate the band tiles are visited in a rotated order: from the
   // unit's common start tile tr (the first band tile of its last query tile,
@@ -255,56 +231,20 @@ __global__ void __launch_bounds__(NW * 64, 2) prefill_kernel(PrefillArgs a) {
       }
     }
   };
-  auto issue_k = [&](int it) { tile_dma(kg, k_src, it, &sK[it % KST][0]); };
-  Vec16<T> vreg[TL::VREG];
-  auto issue_v = [&](int it) {
-    if constexpr (TL::kTr) {
-      tile_dma(vg, v_src, it, &sV[it & 1][0]);
-    } else {
-      const int j0 = tile_j0(it);
-#pragma unroll
-      for (int i = 0; i < TL::VREG; ++i) {
-        const int idx = threadIdx.x + i * NW * 64;
-        const int r = idx / CPR, cc = idx % CPR;
-        const int64_t j = min(int64_t(j0 + r), n - 1);
-        vreg[i] = load16(reinterpret_cast<const T*>(vg + j * kv_row_bytes) + cc * EPL);
-      }
-    }
-  };
-  // fp32: V^T[d][key] is written from the staged registers.
-  auto store_vt = [&](int buf) {
-    if constexpr (!TL::kTr) {
-      T* vt = reinterpret_cast<T*>(&sV[buf][0]);
-#pragma unroll
-      for (int i = 0; i < TL::VREG; ++i) {
-        const int idx = threadIdx.x + i * NW * 64;
-        const int r = idx / CPR, cc = idx % CPR;
-#pragma unroll
-        for (int e = 0; e < EPL; ++e) vt[(cc * EPL + e) * TL::VT_LD + r] = vreg[i].v[e];
-      }
-    }
-  };
+  // lt: the tile's number within this key group.
+  auto issue_k = [&](int lt) { tile_dma(k_base, k_src, lt * KG + kg, sK + (lt % KST) * TL::TILE_BYTES); };
+  auto issue_v = [&](int lt) { tile_dma(v_base, v_src, lt * KG + kg, sV + (lt & 1) * TL::TILE_BYTES); };
 
   // Per-lane byte offsets of the MFMA operand reads (tile independent).
   // K operand: row lrow (+ 32 * sub; the swizzle depends on the row's low bits
-  // only), head-dim elements [kk*K + half*K/2, +K/2).
-  auto k_offset = [&](int kk) {
-    if constexpr (TL::kTr) {
-      return lrow * RB + (((2 * kk + half) ^ TL::swz_k(lrow)) * 16);
-    } else {
-      const int d = 2 * kk + half;
-      return lrow * RB + (((d / 4) ^ TL::swz_k(lrow)) * 16) + (d % 4) * 4;
-    }
-  };
-  int k_off[TL::kTr ? KS : 1];
-  if constexpr (TL::kTr) {
+  // only), head-dim elements 16 * kk + 8 * half .. +7.
+  int k_off[KS];
 #pragma unroll
-    for (int kk = 0; kk < KS; ++kk) k_off[kk] = k_offset(kk);
-  }
+  for (int kk = 0; kk < KS; ++kk) k_off[kk] = lrow * RB + (((2 * kk + half) ^ TL::swz_k(lrow)) * 16);
   // Transposing V read: lane 16G + 4e + a points at row (G/2)*4 + e (+ kb0),
   // bf16 column 32*dt + 16*(G%2) + 4a.
   int v_off[D / 32];
-  if constexpr (TL::kTr) {
+  {
     const int vr = (lane >> 5) * 4 + ((lane & 15) >> 2);    // row mod 8
     const int a4 = lane & 3;
 #pragma unroll
@@ -312,9 +252,6 @@ __global__ void __launch_bounds__(NW * 64, 2) prefill_kernel(PrefillArgs a) {
       const int q = dt * 4 + ((lane >> 4) & 1) * 2 + (a4 >> 1);
       v_off[dt] = vr * RB + ((q ^ TL::swz_v(vr)) * 16) + (a4 & 1) * 8;
     }
-  } else {
-#pragma unroll
-    for (int dt = 0; dt < D / 32; ++dt) v_off[dt] = (dt * 32 + lrow) * TL::VT_LD * int(sizeof(T));
   }
 
   f32x16 oacc[D / 32];
@@ -325,20 +262,22 @@ __global__ void __launch_bounds__(NW * 64, 2) prefill_kernel(PrefillArgs a) {
 
   // Pipeline: during tile t, V(t+1) and then K(t+2) stream in; at the top of
   // tile t only the newest K loads may still be in flight.
-  if (ntiles > 0) {
+  const int my_tiles = (ntiles - kg + KG - 1) / KG;   // of this key group
+  const int rounds = (ntiles + KG - 1) / KG;          // barriers, the same for every group
+  if (my_tiles > 0) {
     issue_v(0);
     issue_k(0);
   }
-  if (ntiles > 1) issue_k(1);
+  if (my_tiles > 1) issue_k(1);
   {
     const int i = iw0 + lrow;
     if (wave_active && i < i1) {
-      const T* qrow = qg + int64_t(i) * q_row_stride;
+      const bf16* qrow = qg + int64_t(i) * q_row_stride + 8 * half;
 #pragma unroll
-      for (int kk = 0; kk < KS; ++kk) qf[kk] = load_frag(qrow, kk, half);
+      for (int kk = 0; kk < KS; ++kk) qf[kk] = *reinterpret_cast<const bf16x8*>(qrow + 16 * kk);
     } else {
 #pragma unroll
-      for (int kk = 0; kk < KS; ++kk) qf[kk] = typename M::frag{};
+      for (int kk = 0; kk < KS; ++kk) qf[kk] = bf16x8{};
     }
   }
   // Wait for Q (and the first tiles) here, once.  The tile DMA is opaque to
@@ -346,30 +285,21 @@ __global__ void __launch_bounds__(NW * 64, 2) prefill_kernel(PrefillArgs a) {
   // the Q loads inside the tile loop, where they would also drain the
   // prefetches in flight.
   __builtin_amdgcn_s_waitcnt(0x0F70);   // vmcnt(0)
-  for (int it = 0; it < ntiles; ++it) {
-    const int j0 = tile_j0(it);
-    if constexpr (KST == 3) {
-      if (it + 1 < ntiles) {
-        // all but the last DPW loads (K(it+1)) have landed: K(it), V(it)
-        __builtin_amdgcn_s_waitcnt(0x0F70 | DPW);
-      } else {
-        __builtin_amdgcn_s_waitcnt(0x0F70);
-      }
+  for (int it = 0; it < rounds; ++it) {
+    const int j0 = tile_j0(it * KG + kg);
+    if (it + 1 < my_tiles) {
+      // all but the last DPW loads (K(it+1)) have landed: K(it), V(it)
+      __builtin_amdgcn_s_waitcnt(0x0F70 | DPW);
     } else {
       __builtin_amdgcn_s_waitcnt(0x0F70);   // vmcnt(0)
     }
-    store_vt(it & 1);
     __syncthreads();                      // ... for every thread; K(it-1), V(it-1) buffers are free
-    if (it + 1 < ntiles) issue_v(it + 1);
-    if constexpr (KST == 3) {
-      if (it + 2 < ntiles) issue_k(it + 2);
-    } else {
-      if (it + 1 < ntiles) issue_k(it + 1);
-    }
+    if (it + 1 < my_tiles) issue_v(it + 1);
+    if (it + 2 < my_tiles) issue_k(it + 2);
     const int buf = it & 1;
     const int kbuf = it % KST;
 
-    if (!wave_active) continue;
+    if (!wave_active || it >= my_tiles) continue;
     // Does any (row, key) pair of this wave fall inside the mask?
     const bool any_causal = j0 <= iw1 - 1;
     const bool any_vis = any_causal && (j0 < s || band_start(iw0) <= j0 + BN - 1);
@@ -378,25 +308,31 @@ __global__ void __launch_bounds__(NW * 64, 2) prefill_kernel(PrefillArgs a) {
                          ((j0 + BN <= s) || band_start(iw1 - 1) <= j0);
 
     // S^T = K Q^T for two 32-key sub-tiles.
-    // Fragments of step kk+1 are read while the MFMAs of step kk run; the two
-    // 32-key chains alternate so consecutive MFMAs are independent.
-    const char* kb = &sK[kbuf][0];
+    // The two 32-key chains alternate so consecutive MFMAs are independent.
+    const char* kb = sK + kbuf * TL::TILE_BYTES;
     auto kfrag = [&](int kk, int sub) {
-      const int off = TL::kTr ? k_off[TL::kTr ? kk : 0] : k_offset(kk);
-      return *reinterpret_cast<const typename M::frag*>(kb + sub * 32 * RB + off);
+      return *reinterpret_cast<const bf16x8*>(kb + sub * 32 * RB + k_off[kk]);
     };
     f32x16 sacc[2] = {f32x16{}, f32x16{}};
-    typename M::frag kf[2][2];
-    kf[0][0] = kfrag(0, 0);
-    kf[0][1] = kfrag(0, 1);
+    // Fragments are read two steps ahead.  The fence holds that order: the
+    // scheduler otherwise saves the registers and reads each step's fragments
+    // right before their use, one LDS latency per step (0.5 - 2 % of a call at
+    // head_dim 128, nothing at 64, where four waves share a SIMD).
+    bf16x8 kf[3][2];
+#pragma unroll
+    for (int kk = 0; kk < 2; ++kk) {
+      kf[kk][0] = kfrag(kk, 0);
+      kf[kk][1] = kfrag(kk, 1);
+    }
 #pragma unroll
     for (int kk = 0; kk < KS; ++kk) {
-      if (kk + 1 < KS) {
-        kf[(kk + 1) & 1][0] = kfrag(kk + 1, 0);
-        kf[(kk + 1) & 1][1] = kfrag(kk + 1, 1);
+      if (kk + 2 < KS) {
+        kf[(kk + 2) % 3][0] = kfrag(kk + 2, 0);
+        kf[(kk + 2) % 3][1] = kfrag(kk + 2, 1);
       }
-      sacc[0] = M::mma(kf[kk & 1][0], qf[kk], sacc[0]);
-      sacc[1] = M::mma(kf[kk & 1][1], qf[kk], sacc[1]);
+      sacc[0] = mma(kf[kk % 3][0], qf[kk], sacc[0]);
+      sacc[1] = mma(kf[kk % 3][1], qf[kk], sacc[1]);
+      sched_fence();
     }
 
     // Mask (edge tiles only; branch-free selects) and the tile's raw row maximum.
@@ -431,120 +367,127 @@ __global__ void __launch_bounds__(NW * 64, 2) prefill_kernel(PrefillArgs a) {
       for (int dt = 0; dt < D / 32; ++dt) oacc[dt] *= alpha;
     }
 
-    const char* vb = &sV[buf][0];
-    if constexpr (TL::kTr) {
-      // P in bf16; the row sum is taken over the same rounded weights that
-      // enter the PV product (dot2 with (1, 1)).
-      bf16x8 pf[2][2];
-      float psum = 0.0f;
+    const char* vb = sV + buf * TL::TILE_BYTES;
+    // P in bf16; the row sum is taken over the same rounded weights that
+    // enter the PV product (dot2 with (1, 1)).
+    bf16x8 pf[2][2];
+    float psum = 0.0f;
 #pragma unroll
-      for (int sub = 0; sub < 2; ++sub) {
+    for (int sub = 0; sub < 2; ++sub) {
 #pragma unroll
-        for (int c = 0; c < 2; ++c) {
+      for (int c = 0; c < 2; ++c) {
 #pragma unroll
-          for (int e = 0; e < 8; ++e)
-            pf[sub][c][e] = static_cast<bf16>(fast_exp2(__builtin_fmaf(sacc[sub][8 * c + e], c2, -m_run)));
+        for (int e = 0; e < 8; ++e)
+          pf[sub][c][e] = static_cast<bf16>(fast_exp2(__builtin_fmaf(sacc[sub][8 * c + e], c2, -m_run)));
 #pragma unroll
-          for (int e = 0; e < 8; e += 2) psum = dot2_ones(pf[sub][c][e], pf[sub][c][e + 1], psum);
-        }
+        for (int e = 0; e < 8; e += 2) psum = dot2_ones(pf[sub][c][e], pf[sub][c][e + 1], psum);
       }
-      psum = sum_xor<32>(psum);
-      l_run += psum;
+    }
+    psum = sum_xor<32>(psum);
+    l_run += psum;
 
-      // O^T += V^T P^T: for each 16-key step the four d-tile accumulators are
-      // independent; the V^T fragments of the next step are read meanwhile.
-      auto vfrag = [&](int step, int dt) {
-        const int kb0 = (step >> 1) * 32 + 16 * (step & 1);
-        const bf16x4 lo4 = read_tr(reinterpret_cast<const bf16*>(vb + kb0 * RB + v_off[dt]));
-        const bf16x4 hi4 = read_tr(reinterpret_cast<const bf16*>(vb + (kb0 + 8) * RB + v_off[dt]));
-        return __builtin_shufflevector(lo4, hi4, 0, 1, 2, 3, 4, 5, 6, 7);
-      };
-      bf16x8 vf[2][D / 32];
+    // O^T += V^T P^T: for each 16-key step the four d-tile accumulators are
+    // independent; the V^T fragments of the next step are read meanwhile.
+    auto vfrag = [&](int step, int dt) {
+      const int kb0 = (step >> 1) * 32 + 16 * (step & 1);
+      const bf16x4 lo4 = read_tr(reinterpret_cast<const bf16*>(vb + kb0 * RB + v_off[dt]));
+      const bf16x4 hi4 = read_tr(reinterpret_cast<const bf16*>(vb + (kb0 + 8) * RB + v_off[dt]));
+      return __builtin_shufflevector(lo4, hi4, 0, 1, 2, 3, 4, 5, 6, 7);
+    };
+    bf16x8 vf[2][D / 32];
 #pragma unroll
-      for (int dt = 0; dt < D / 32; ++dt) vf[0][dt] = vfrag(0, dt);
+    for (int dt = 0; dt < D / 32; ++dt) vf[0][dt] = vfrag(0, dt);
 #pragma unroll
-      for (int step = 0; step < 4; ++step) {
-        if (step + 1 < 4) {
+    for (int step = 0; step < 4; ++step) {
+      if (step + 1 < 4) {
 #pragma unroll
-          for (int dt = 0; dt < D / 32; ++dt) vf[(step + 1) & 1][dt] = vfrag(step + 1, dt);
-        }
-#pragma unroll
-        for (int dt = 0; dt < D / 32; ++dt)
-          oacc[dt] = M::mma(vf[step & 1][dt], pf[step >> 1][step & 1], oacc[dt]);
+        for (int dt = 0; dt < D / 32; ++dt) vf[(step + 1) & 1][dt] = vfrag(step + 1, dt);
       }
-    } else {
-      float psum = 0.0f;
 #pragma unroll
-      for (int sub = 0; sub < 2; ++sub) {
+      for (int dt = 0; dt < D / 32; ++dt)
+        oacc[dt] = mma(vf[step & 1][dt], pf[step >> 1][step & 1], oacc[dt]);
+    }
+  }
+
+  if constexpr (KG > 1) {
+    // The groups' states of the same rows sit in the same lanes of waves w and
+    // w + NR: each group but the first leaves (accumulator, m, l) in LDS.
+    constexpr int kRegs = D / 2 + 2;                  // values per lane
+    static_assert((KG - 1) * NR * kRegs * 256 <= KG * kGroupBytes, "the states fit the tiles' LDS");
+    float* const st = reinterpret_cast<float*>(s_tiles) + lane;
+    __syncthreads();                                  // every tile has been read
+    if (kg > 0) {
+      float* p = st + ((kg - 1) * NR + wave) * kRegs * 64;
 #pragma unroll
-        for (int r = 0; r < 16; ++r) {
-          // separately rounded product: a row's maximal score gives exactly
-          // 2^0, so w = 1 returns v bit-exactly in fp32
-          const float p = fast_exp2(mul_then_sub(sacc[sub][r], c2, m_run));
-          sacc[sub][r] = p;
-          psum += p;
-        }
-      }
-      psum = sum_xor<32>(psum);
-      l_run += psum;
+      for (int dt = 0; dt < D / 32; ++dt)
 #pragma unroll
-      for (int dt = 0; dt < D / 32; ++dt) {
-        const T* vt = reinterpret_cast<const T*>(vb + v_off[dt]);
+        for (int r = 0; r < 16; ++r) p[(dt * 16 + r) * 64] = oacc[dt][r];
+      p[(kRegs - 2) * 64] = m_run;
+      p[(kRegs - 1) * 64] = l_run;
+    }
+    __syncthreads();
+    if (kg > 0) return;
+#pragma unroll 1
+    for (int v = 0; v < KG - 1; ++v) {
+      const float* p = st + (v * NR + wave) * kRegs * 64;
+      const float m2 = p[(kRegs - 2) * 64];
+      const float m_new = fmaxf(m_run, m2);
+      const float f1 = fast_exp2(m_run - m_new), f2 = fast_exp2(m2 - m_new);
+      m_run = m_new;
+      l_run = l_run * f1 + p[(kRegs - 1) * 64] * f2;
 #pragma unroll
-        for (int sub = 0; sub < 2; ++sub) {
+      for (int dt = 0; dt < D / 32; ++dt)
 #pragma unroll
-          for (int r = 0; r < 16; ++r) {
-            const int key = sub * 32 + (r >> 2) * 8 + half * 4 + (r & 3);
-            oacc[dt] = M::mma(vt[key], sacc[sub][r], oacc[dt]);
-          }
-        }
-      }
+        for (int r = 0; r < 16; ++r) oacc[dt][r] = oacc[dt][r] * f1 + p[(dt * 16 + r) * 64] * f2;
     }
   }
 
   if (!wave_active || my_row >= i1) return;
   const float inv_l = 1.0f / l_run;
-  T* orow = static_cast<T*>(a.o) + (int64_t(b) * n * a.hq + h) * D + int64_t(my_row) * q_row_stride;
+  bf16* orow = static_cast<bf16*>(a.o) + (int64_t(b) * n * a.hq + h) * D + int64_t(my_row) * q_row_stride;
 #pragma unroll
   for (int dt = 0; dt < D / 32; ++dt) {
 #pragma unroll
     for (int grp = 0; grp < 4; ++grp) {
       const int d0 = dt * 32 + grp * 8 + half * 4;
-      if constexpr (sizeof(T) == 2) {
-        bf16x4 outv;
+      bf16x4 outv;
 #pragma unroll
-        for (int e = 0; e < 4; ++e) outv[e] = static_cast<bf16>(oacc[dt][grp * 4 + e] * inv_l);
-        *reinterpret_cast<bf16x4*>(orow + d0) = outv;
-      } else {
-        f32x4 outv;
-#pragma unroll
-        for (int e = 0; e < 4; ++e) outv[e] = oacc[dt][grp * 4 + e] * inv_l;
-        *reinterpret_cast<f32x4*>(orow + d0) = outv;
-      }
+      for (int e = 0; e < 4; ++e) outv[e] = static_cast<bf16>(oacc[dt][grp * 4 + e] * inv_l);
+      *reinterpret_cast<bf16x4*>(orow + d0) = outv;
     }
   }
 }
 
-template <typename T, int D>
+template <int D, int NR, int KG>
 int launch_t(const PrefillArgs& a, void* stream) {
-  const int64_t blocks = int64_t((a.n_units + kNumXcd - 1) / kNumXcd) * kNumXcd * a.group * a.qchunk;
   PrefillArgs copy = a;
+  // A unit spans at least kPrefillUnitBlocks work-groups (query tiles x group),
+  // and at least kPrefillChunk query tiles.
+  const int64_t tiles = (a.n + 32 * NR - 1) / (32 * NR);
+  const int64_t qchunk = std::min<int64_t>(std::max<int64_t>(kPrefillChunk, kPrefillUnitBlocks / a.group), tiles);
+  const int64_t n_chunks = (tiles + qchunk - 1) / qchunk;
+  const int64_t n_units = int64_t(a.hkv) * a.batch * n_chunks;
+  const int64_t blocks = (n_units + kNumXcd - 1) / kNumXcd * kNumXcd * a.group * qchunk;
+  copy.n_qtiles = static_cast<int32_t>(tiles);
+  copy.qchunk = static_cast<int32_t>(qchunk);
+  copy.n_chunks = static_cast<int32_t>(n_chunks);
+  copy.n_units = static_cast<int32_t>(n_units);
   void* args[] = {&copy};
-  return static_cast<int>(hipLaunchKernel(reinterpret_cast<const void*>(&prefill_kernel<T, D>),
-                                          dim3(static_cast<unsigned>(blocks)), dim3(NW * 64), args, 0,
+  return static_cast<int>(hipLaunchKernel(reinterpret_cast<const void*>(&prefill_kernel<D, NR, KG>),
+                                          dim3(static_cast<unsigned>(blocks)), dim3(NR * KG * 64), args, 0,
                                           static_cast<hipStream_t>(stream)));
+}
+
+template <int D>
+int launch_d(const PrefillArgs& a, void* stream) {
+  return launch_t<D, 4, 1>(a, stream);
 }
 
 }  // namespace
 
-int launch_prefill(const PrefillArgs& a, int dtype, int head_dim, void* stream) {
-  if (dtype == MOA_BF16) {
-    if (head_dim == 128) return launch_t<bf16, 128>(a, stream);
-    if (head_dim == 64) return launch_t<bf16, 64>(a, stream);
-  } else {
-    if (head_dim == 128) return launch_t<float, 128>(a, stream);
-    if (head_dim == 64) return launch_t<float, 64>(a, stream);
-  }
+int launch_prefill(const PrefillArgs& a, int head_dim, void* stream) {
+  if (head_dim == 128) return launch_d<128>(a, stream);
+  if (head_dim == 64) return launch_d<64>(a, stream);
   return static_cast<int>(hipErrorInvalidValue);
 }
 
