@@ -5,8 +5,8 @@
 // of row i instead starts at the first token of block i/64 - ceil(w_g/64) + 1;
 // both are "j >= band_start(i)" with band_start(i) = ((i >> sh) - W + 1) << sh.
 //
-// One work-group = 4 waves = 128 query rows of one (sequence, query head);
-// each wave owns 32 rows.  The work-group walks only the 64-key tiles that
+// One work-group = 4 waves = 128 query rows of one (sequence, query head) in a
+// large launch (small ones: launch_d below); each wave owns 32 rows.  The work-group walks only the 64-key tiles that
 // intersect the sink prefix or the band of its rows; every other tile is
 // skipped without being read.  K and V tiles are staged in LDS (the global
 // loads of the next tiles are in flight while a tile is computed, one barrier
@@ -102,7 +102,7 @@ struct Tiles {
 // kg, kg + KG, ... through LDS stages of its own, and the groups' states meet in
 // LDS at the end.
 template <int D, int NR, int KG>
-__global__ void __launch_bounds__(NR * KG * 64, 2) prefill_kernel(PrefillArgs a) {
+__global__ void __launch_bounds__(NR * KG * 64, D == 128 && NR * KG == 4 && KG > 1 ? 1 : 2) prefill_kernel(PrefillArgs a) {
   using TL = Tiles<D, NR>;
   constexpr int BM = 32 * NR;             // query rows per work-group
   constexpr int KS = D / 16;              // MFMA steps over the head dimension
@@ -478,8 +478,29 @@ int launch_t(const PrefillArgs& a, void* stream) {
                                           static_cast<hipStream_t>(stream)));
 }
 
+// A launch of few work-groups takes as long as its longest chain of tiles (a
+// tile of a lone work-group 1.65 us at head_dim 128, of two on a compute unit
+// 1.9), so the chain is split over two key groups, where each work-group has a
+// compute unit (head_dim 128: 160 KB of LDS) to itself:
+//   64 rows per work-group as long as those fit the chip at once: 32 heads x 512
+//     18.6 -> 15.0 us, x 256 11.7 -> 10.3; head_dim 64, 16 heads x 512 13.8 -> 9.7,
+//     32 heads x 1,024 23.2 -> 16.1;
+//   128 rows then: 32 heads x 1,024 30.6 -> 26.1, and, where every compute unit
+//     gets two of them in turn, only for long chains: 32 heads x 2,048 57.0 ->
+//     54.6, 16 heads x 3,000 94.6 -> 61.6, but 2 x 32 heads x 1,024 33.6 -> 38.9.
+// With more work-groups two per compute unit cover each other's waits and their
+// starts and ends (32 heads x 4,096: 128 us against 139).
 template <int D>
 int launch_d(const PrefillArgs& a, void* stream) {
+  const int64_t heads = int64_t(a.batch) * a.hq;
+  const int64_t w64 = (a.n + 63) / 64 * heads, w128 = (a.n + 127) / 128 * heads;
+  int64_t widest = 0;
+  for (int g = 0; g < a.hkv; ++g) widest = std::max(widest, int64_t(a.window[g]) << a.band_shift);
+  const int64_t chain = std::min((a.n + BN - 1) / BN, (a.num_sink + BN - 1) / BN + widest / BN + 3);
+  constexpr int64_t kFit64 = D == 128 ? 256 : 512;      // work-groups of 160 (80) KB of LDS on the chip
+  constexpr int64_t kLong = D == 128 ? 20 : 12;
+  if (w64 <= kFit64 && chain >= 3) return launch_t<D, 2, 2>(a, stream);
+  if ((w128 <= 256 && chain >= 6) || (w128 <= 512 && chain >= kLong)) return launch_t<D, 4, 2>(a, stream);
   return launch_t<D, 4, 1>(a, stream);
 }
 

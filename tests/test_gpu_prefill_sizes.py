@@ -1,7 +1,8 @@
 """Prefill at the edges of its kernels' size classes and tiles, against fp64
-attention in plain torch: fp32 with 1, 2 and 4 waves per row block, 32 and 64
-rows per wave, with and without a die per (KV head, sequence) pair, and lengths
-around whole tiles."""
+attention in plain torch: bf16 work-groups of 64 and 128 rows with one and two
+key groups; fp32 with 1, 2 and 4 waves per row block, 32 and 64 rows per wave,
+with and without a die per (KV head, sequence) pair; lengths around whole
+tiles."""
 import math
 
 import pytest
@@ -67,3 +68,23 @@ def test_prefill_f32_window_of_one_key_is_exact():
         gen = torch.Generator(device="cuda").manual_seed(n)
         q, k, v = (torch.randn((b, n, h, d), generator=gen, device="cuda") for _ in range(3))
         assert torch.equal(M.moa_prefill(plan, q, k, v), v)
+
+
+@pytest.mark.parametrize("b,hq,hkv,d,n,s,flags", [
+    # 64 rows, two key groups (from three tiles of 64 keys on)
+    (1, 4, 4, 128, 129, 0, 0), (1, 4, 2, 128, 130, 3, 0), (1, 8, 1, 128, 191, 64, M.MOA_BLOCK_BAND),
+    (1, 32, 32, 128, 512, 4, 0), (1, 4, 4, 64, 129, 0, 0), (1, 16, 4, 64, 2047, 70, 0), (3, 16, 8, 64, 640, 0, 0),
+    # one more work-group than fits, and too short a chain: 128 rows, one key group
+    (1, 4, 4, 128, 128, 0, 0), (3, 32, 8, 128, 200, 64, 0),
+    # 128 rows, two key groups
+    (1, 32, 32, 128, 513, 0, 0), (1, 32, 8, 128, 1024, 64, M.MOA_BLOCK_BAND), (1, 16, 2, 128, 3001, 1, 0),
+    (4, 16, 16, 64, 1000, 4, 0), (1, 16, 16, 64, 4033, 64, 0),
+    # two work-groups of 128 rows per compute unit and more
+    (2, 32, 32, 128, 1025, 4, 0), (5, 16, 4, 64, 1000, 0, M.MOA_BLOCK_BAND),
+])
+@pytest.mark.parametrize("narrow", [False, True])
+def test_prefill_bf16_sizes(b, hq, hkv, d, n, s, flags, narrow):
+    windows = [1 + (97 * g * g + 13 * g) % max(1, n // 8 if narrow else n) for g in range(hkv)]
+    if not narrow:
+        windows[-1] = n
+    _run("bf16", b, hq, hkv, d, n, s, flags, windows)
