@@ -32,6 +32,7 @@
 // offset.  The mask is evaluated only on tiles that are not entirely visible
 // to the wave's rows.
 #include <algorithm>
+#include <type_traits>
 
 #include "moa_device.h"
 
@@ -337,13 +338,21 @@ __global__ void __launch_bounds__(NR * KG * 64, D == 128 && NR * KG == 4 && KG >
       __builtin_amdgcn_s_waitcnt(0x0F70);   // vmcnt(0)
     }
     __syncthreads();                      // ... for every thread; K(it-1), V(it-1) buffers are free
-    if (it + 1 < my_tiles) tile_dma(v_base, v_src, j1, off1, sV + (v_now ^ TL::TILE_BYTES));
-    if (it + 2 < my_tiles) tile_dma(k_base, k_src, j2, off2, sK + k_next);
 
-    if (!wave_active || it >= my_tiles) continue;
     // Does any (row, key) pair of this wave fall inside the mask?
     const bool any_causal = j0 <= iw1 - 1;
-    const bool any_vis = any_causal && (j0 < s || band_start(iw0) <= j0 + BN - 1);
+    const bool any_vis = wave_active && it < my_tiles && any_causal && (j0 < s || band_start(iw0) <= j0 + BN - 1);
+    // The next tiles' loads go between the S products: issued at once after the
+    // barrier, the loads of all waves queue for the compute unit's one address
+    // unit and the waves stand still meanwhile.  Worth 1 - 4 % at head_dim 128
+    // (32 heads x 2,048: 53.7 -> 51.5 us); at 64, where other waves fill the
+    // gap, it costs 2 %.
+    constexpr bool kSpread = D == 128;
+    const bool spread = kSpread && any_vis && it + 2 < my_tiles && j1 + BN <= n32 && j2 + BN <= n32;
+    if (!spread) {
+      if (it + 1 < my_tiles) tile_dma(v_base, v_src, j1, off1, sV + (v_now ^ TL::TILE_BYTES));
+      if (it + 2 < my_tiles) tile_dma(k_base, k_src, j2, off2, sK + k_next);
+    }
     if (!any_vis) continue;
     const bool all_vis = (j0 + BN - 1 <= iw0) && (iw1 - iw0 == 32) &&
                          ((j0 + BN <= s) || band_start(iw1 - 1) <= j0);
@@ -365,16 +374,54 @@ __global__ void __launch_bounds__(NR * KG * 64, D == 128 && NR * KG == 4 && KG >
       kf[kk][0] = kfrag(kk, 0);
       kf[kk][1] = kfrag(kk, 1);
     }
-#pragma unroll
-    for (int kk = 0; kk < KS; ++kk) {
-      if (kk + 2 < KS) {
-        kf[(kk + 2) % 3][0] = kfrag(kk + 2, 0);
-        kf[(kk + 2) % 3][1] = kfrag(kk + 2, 1);
+    auto products = [&](auto with_loads) {
+      i32x4 rv = {}, rk = {};
+      if constexpr (decltype(with_loads)::value) {
+        const uint32_t bytes = uint32_t(BN - 1) * uint32_t(kv_row_bytes) + RB;
+        rv = make_desc(v_base + off1, bytes);
+        rk = make_desc(k_base + off2, bytes);
       }
-      sacc[0] = mma(kf[kk % 3][0], qf[kk], sacc[0]);
-      sacc[1] = mma(kf[kk % 3][1], qf[kk], sacc[1]);
-      sched_fence();
+#pragma unroll
+      for (int kk = 0; kk < KS; ++kk) {
+        if (kk + 2 < KS) {
+          kf[(kk + 2) % 3][0] = kfrag(kk + 2, 0);
+          kf[(kk + 2) % 3][1] = kfrag(kk + 2, 1);
+        }
+        sacc[0] = mma(kf[kk % 3][0], qf[kk], sacc[0]);
+        sacc[1] = mma(kf[kk % 3][1], qf[kk], sacc[1]);
+        if constexpr (decltype(with_loads)::value) {
+          // V(it + 1) first: only the newest K loads may be in flight at the next tile.
+          constexpr int kPerStep = 2 * DPW / KS;
+#pragma unroll
+          for (int e = 0; e < kPerStep; ++e) {
+            const int m = kk * kPerStep + e;
+            if (m < DPW) dma16_async(rv, v_src[m % DPW], sV + (v_now ^ TL::TILE_BYTES) + (wave * DPW + m) * 1024);
+            else dma16_async(rk, k_src[m % DPW], sK + k_next + (wave * DPW + m - DPW) * 1024);
+          }
+        }
+        sched_fence();
+      }
+    };
+    if constexpr (kSpread) {
+      if (spread) products(std::true_type{});
+      else products(std::false_type{});
+    } else {
+      products(std::false_type{});
     }
+
+    // The first V^T fragments are read here, behind the mask and the weights
+    // (1 - 2 %: 8 x 32 heads x 8,192: 3.19 -> 3.14 ms).
+    const char* vb = sV + v_now;
+    auto vfrag = [&](int step, int dt) {
+      const int kb0 = (step >> 1) * 32 + 16 * (step & 1);
+      const bf16x4 lo4 = read_tr(reinterpret_cast<const bf16*>(vb + kb0 * RB + v_off[dt]));
+      const bf16x4 hi4 = read_tr(reinterpret_cast<const bf16*>(vb + (kb0 + 8) * RB + v_off[dt]));
+      return __builtin_shufflevector(lo4, hi4, 0, 1, 2, 3, 4, 5, 6, 7);
+    };
+    bf16x8 vf[2][D / 32];
+#pragma unroll
+    for (int dt = 0; dt < D / 32; ++dt) vf[0][dt] = vfrag(0, dt);
+    sched_fence();
 
     // Mask (edge tiles only; branch-free selects) and the tile's raw row maximum.
     if (!all_vis) {
@@ -408,7 +455,6 @@ __global__ void __launch_bounds__(NR * KG * 64, D == 128 && NR * KG == 4 && KG >
       for (int dt = 0; dt < D / 32; ++dt) oacc[dt] *= alpha;
     }
 
-    const char* vb = sV + v_now;
     // P in bf16; the row sum is taken over the same rounded weights that
     // enter the PV product (dot2 with (1, 1)).
     bf16x8 pf[2][2];
@@ -427,17 +473,8 @@ __global__ void __launch_bounds__(NR * KG * 64, D == 128 && NR * KG == 4 && KG >
     psum = sum_xor<32>(psum);
     l_run += psum;
 
-    // O^T += V^T P^T: for each 16-key step the four d-tile accumulators are
+    // O^T += V^T P^T: for each 16-key step the d-tile accumulators are
     // independent; the V^T fragments of the next step are read meanwhile.
-    auto vfrag = [&](int step, int dt) {
-      const int kb0 = (step >> 1) * 32 + 16 * (step & 1);
-      const bf16x4 lo4 = read_tr(reinterpret_cast<const bf16*>(vb + kb0 * RB + v_off[dt]));
-      const bf16x4 hi4 = read_tr(reinterpret_cast<const bf16*>(vb + (kb0 + 8) * RB + v_off[dt]));
-      return __builtin_shufflevector(lo4, hi4, 0, 1, 2, 3, 4, 5, 6, 7);
-    };
-    bf16x8 vf[2][D / 32];
-#pragma unroll
-    for (int dt = 0; dt < D / 32; ++dt) vf[0][dt] = vfrag(0, dt);
 #pragma unroll
     for (int step = 0; step < 4; ++step) {
       if (step + 1 < 4) {
