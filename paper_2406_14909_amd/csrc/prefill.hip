@@ -444,10 +444,12 @@ __global__ void __launch_bounds__(NR * KG * 64, D == 128 && NR * KG == 4 && KG >
     for (int sub = 0; sub < 2; ++sub)
 #pragma unroll
       for (int r = 0; r < 16; ++r) tmax = fmaxf(tmax, sacc[sub][r]);
-    tmax = max_xor<32>(tmax) * c2;
-    // Raise the exponent offset only when some row of the wave needs it.
+    tmax *= c2;
+    // Raise the exponent offset only when some row of the wave needs it.  Only
+    // then do the two lanes of a row meet; their sums meet after the last tile
+    // (an exchange of each per tile: 1 - 2 % of a call).
     if (__any(tmax > m_run + kRescaleSlack)) {
-      const float m_new = fmaxf(m_run, tmax);
+      const float m_new = fmaxf(m_run, max_xor<32>(tmax));
       const float alpha = fast_exp2(m_run - m_new);
       m_run = m_new;
       l_run *= alpha;
@@ -470,7 +472,6 @@ __global__ void __launch_bounds__(NR * KG * 64, D == 128 && NR * KG == 4 && KG >
         for (int e = 0; e < 8; e += 2) psum = dot2_ones(pf[sub][c][e], pf[sub][c][e + 1], psum);
       }
     }
-    psum = sum_xor<32>(psum);
     l_run += psum;
 
     // O^T += V^T P^T: for each 16-key step the d-tile accumulators are
@@ -487,6 +488,7 @@ __global__ void __launch_bounds__(NR * KG * 64, D == 128 && NR * KG == 4 && KG >
     }
   }
 
+  l_run = sum_xor<32>(l_run);
   if constexpr (KG > 1) {
     // The groups' states of the same rows sit in the same lanes of waves w and
     // w + NR: each group but the first leaves (accumulator, m, l) in LDS.

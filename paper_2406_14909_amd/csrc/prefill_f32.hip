@@ -213,10 +213,11 @@ __global__ void __launch_bounds__(NW * 64, D == 64 ? 2 : 1) prefill_f32_kernel(P
       float tmax = -INFINITY;
 #pragma unroll
       for (int r = 0; r < 16; ++r) tmax = fmaxf(tmax, sacc[w][r]);
-      tmax = max_xor<32>(tmax) * c2;
+      tmax *= c2;
       // The exponent offset is raised only when some row of the wave needs it.
+      // Only then do the two lanes of a row meet; their sums meet at the end.
       if (__any(tmax > m_run[w] + kRescaleSlack)) {
-        const float m_new = fmaxf(m_run[w], tmax);
+        const float m_new = fmaxf(m_run[w], max_xor<32>(tmax));
         const float alpha = fast_exp2(m_run[w] - m_new);
         m_run[w] = m_new;
         l_run[w] *= alpha;
@@ -229,7 +230,7 @@ __global__ void __launch_bounds__(NW * 64, D == 64 ? 2 : 1) prefill_f32_kernel(P
         sacc[w][r] = fast_exp2(mul_then_sub(sacc[w][r], c2, m_run[w]));
         psum += sacc[w][r];
       }
-      l_run[w] += sum_xor<32>(psum);
+      l_run[w] += psum;
     }
 #pragma unroll
     for (int r = 0; r < 16; ++r)
@@ -240,6 +241,8 @@ __global__ void __launch_bounds__(NW * 64, D == 64 ? 2 : 1) prefill_f32_kernel(P
     sched_fence();
   }
 
+#pragma unroll
+  for (int w = 0; w < RW; ++w) l_run[w] = sum_xor<32>(l_run[w]);
   if constexpr (KG > 1) {
     // The states of the same rows sit in the same lanes of waves rb + RB * kg.
     constexpr int kBlock = kRegs / RW;                   // values of one block of 32 rows
