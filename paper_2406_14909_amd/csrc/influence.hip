@@ -59,8 +59,9 @@ __global__ void __launch_bounds__(INW * 64, 2) influence_kernel(InfluenceArgs a)
   constexpr int TILE = IBN * RB;          // one K or V tile (rows unpadded)
   constexpr int DPW = TILE / 1024 / INW;  // 1 KB direct-to-LDS loads per wave per tile
 
-  __shared__ __attribute__((aligned(1024))) char sK[2][TILE];
-  __shared__ __attribute__((aligned(1024))) char sV[2][TILE];
+  // K stages 0 and 1, then V stages 0 and 1: one lane address serves all
+  // operand reads of a head-dimension step, the rest are instruction offsets.
+  __shared__ __attribute__((aligned(1024))) char sKV[4 * TILE];
   __shared__ float s_part[INW][kMaxBlocks];     // per-wave block sums
 
   const int lane = threadIdx.x & 63;
@@ -95,28 +96,42 @@ __global__ void __launch_bounds__(INW * 64, 2) influence_kernel(InfluenceArgs a)
   // m / CPR, position m % CPR) and carrying global chunk position ^ swz(row).
   auto swz = [](int r) { return CPR >= 16 ? (r & 15) : ((r >> 1) & 7); };
   uint32_t chunk_off[DPW];
-  int src_row[DPW];
+  const uint32_t src_off = uint32_t((wave * DPW * 64 + lane) / CPR) * kv_row_bytes;   // row of load 0
 #pragma unroll
   for (int i = 0; i < DPW; ++i) {
     const int m = (wave * DPW + i) * 64 + lane;
-    const int r = m / CPR, pos = m % CPR;
-    src_row[i] = r;
-    chunk_off[i] = uint32_t(pos ^ swz(r)) * 16u;
+    chunk_off[i] = uint32_t((m % CPR) ^ swz(m / CPR)) * 16u;
   }
   // Tile `it` of item b into buffer `buf`.  The buffer resource spans the
   // item's n key rows of head g; rows past n re-read row n - 1 (never
   // visible).
-  const uint32_t span = uint32_t(n - 1) * kv_row_bytes + RB;
+  const uint32_t last_row = uint32_t(n - 1) * kv_row_bytes;
+  const uint32_t span = last_row + RB;
   auto issue = [&](int b, int it, int buf) {
     const int64_t first = int64_t(b) * n * a.hkv + g;             // row 0 of head g, in rows of D
     const i32x4 kd = make_desc(static_cast<const char*>(a.k) + first * RB, span);
     const i32x4 vd = make_desc(static_cast<const char*>(a.v) + first * RB, span);
+    const uint32_t tile_off = uint32_t(it * IBN) * kv_row_bytes;
 #pragma unroll
     for (int i = 0; i < DPW; ++i) {
-      const uint32_t off = uint32_t(min(it * IBN + src_row[i], n - 1)) * kv_row_bytes + chunk_off[i];
-      dma16_async(kd, off, &sK[buf][(wave * DPW + i) * 1024]);
-      dma16_async(vd, off, &sV[buf][(wave * DPW + i) * 1024]);
+      const uint32_t row_off = src_off + (tile_off + uint32_t(i * (64 / CPR)) * kv_row_bytes);
+      const uint32_t off = min(row_off, last_row) + chunk_off[i];
+      dma16_async(kd, off, sKV + buf * TILE + (wave * DPW + i) * 1024);
+      dma16_async(vd, off, sKV + (2 + buf) * TILE + (wave * DPW + i) * 1024);
     }
+  };
+  // The vector unit bounds the kernel, so addresses are kept, not formed: a pass
+  // over a tile took 37 integer adds and 8 quarter-rate products of its 206 - 253
+  // vector instructions, now 20 at full rate (2 x 32 heads x 4,096: 580 -> 564 us,
+  // 32 heads x 8,192: 1,083 -> 1,042, head_dim 64, 2 x 32 x 4,096: 359 -> 348).
+  // Offset in the current stage of this lane's operand chunk of row lrow (the
+  // swizzle of row lrow + 32 is the same), for each head-dimension step.
+  int frag_off[KS];
+#pragma unroll
+  for (int kk = 0; kk < KS; ++kk) frag_off[kk] = lrow * RB + ((2 * kk + half) ^ swz(lrow)) * 16;
+  auto other_stage = [&] {
+#pragma unroll
+    for (int kk = 0; kk < KS; ++kk) frag_off[kk] ^= TILE;
   };
 
   struct Acc {                                    // S^T and dP^T of 32 keys
@@ -160,6 +175,9 @@ __global__ void __launch_bounds__(INW * 64, 2) influence_kernel(InfluenceArgs a)
   };
   // Pass 2, one element: A / (1 - A) = 1 / (2^(lse2 - c2 s) - 1), and the
   // tile's influence sum is  sum -ratio * (dP - D) = D * sum ratio - sum ratio * dP.
+  // (dP products that start from -D would save the sum of the ratios, 0 - 4 %
+  // of the time, but round differently from pass 1's: in a row whose largest A is close
+  // to 1, dP - D is a small difference and the block means were off by 1e-3.)
   auto influence = [&](float sv, float dv) {
     const float inv_p = fast_exp2(__builtin_fmaf(sv, -c2, lse2));
     const float ratio = __builtin_amdgcn_rcpf(inv_p - 1.0f);
@@ -204,22 +222,19 @@ __global__ void __launch_bounds__(INW * 64, 2) influence_kernel(InfluenceArgs a)
     mr = kNegBig;
     l = u = lse2 = drow = acc_dp = acc_r = 0.0f;
 
-    // One pipelined step: the products of half `sub` of LDS buffer `buf`
+    // One pipelined step: the products of half `sub` of the current LDS stage
     // into `out` (kProd), written interleaved with the vector work of the
     // previous half `in` (kWork) in KS groups: each group reads the operands
     // of two groups later from LDS, issues its two MFMAs and then 16 / KS elements of
     // vector work, which run while the matrix core is busy.  The scheduling
     // barrier after each group keeps that order.
-    auto step = [&](auto second_c, auto prod_c, auto work_c, int buf, int sub, Acc& out, const Acc& in) {
+    auto step = [&](auto second_c, auto prod_c, auto work_c, int sub, Acc& out, const Acc& in) {
       constexpr bool kSecond = decltype(second_c)::value;
       constexpr bool kProd = decltype(prod_c)::value;
       constexpr bool kWork = decltype(work_c)::value;
       constexpr int EPG = 16 / KS;                  // elements of work per group
-      const int r = sub * 32 + lrow;
-      const char* kb = &sK[buf][r * RB];
-      const char* vb = &sV[buf][r * RB];
-      auto frag = [&](const char* base, int kk) {
-        return *reinterpret_cast<const bf16x8*>(base + ((2 * kk + half) ^ swz(r)) * 16);
+      auto frag = [&](int stage, int kk) {
+        return *reinterpret_cast<const bf16x8*>(sKV + frag_off[kk] + (stage * TILE + sub * 32 * RB));
       };
       bf16x8 kf[3], vf[3];                          // operands read two groups ahead
       float m_new = 0.0f;
@@ -228,8 +243,8 @@ __global__ void __launch_bounds__(INW * 64, 2) influence_kernel(InfluenceArgs a)
         out.d = f32x16{};
 #pragma unroll
         for (int kk = 0; kk < 2; ++kk) {
-          kf[kk] = frag(kb, kk);
-          vf[kk] = frag(vb, kk);
+          kf[kk] = frag(0, kk);
+          vf[kk] = frag(2, kk);
         }
       }
       if constexpr (kWork && !kSecond) m_new = rescale(in);
@@ -237,8 +252,8 @@ __global__ void __launch_bounds__(INW * 64, 2) influence_kernel(InfluenceArgs a)
       for (int kk = 0; kk < KS; ++kk) {
         if constexpr (kProd) {
           if (kk + 2 < KS) {
-            kf[(kk + 2) % 3] = frag(kb, kk + 2);
-            vf[(kk + 2) % 3] = frag(vb, kk + 2);
+            kf[(kk + 2) % 3] = frag(0, kk + 2);
+            vf[(kk + 2) % 3] = frag(2, kk + 2);
           }
           out.s = mma32(kf[kk % 3], qf[kk], out.s);
           out.d = mma32(vf[kk % 3], df[kk], out.d);
@@ -278,26 +293,29 @@ __global__ void __launch_bounds__(INW * 64, 2) influence_kernel(InfluenceArgs a)
       Acc acc0, acc1;
       tile_ready(0);
       if (wave_active) {
-        step(second_c, yes, no, buf(0), 0, acc0, acc1);
+        step(second_c, yes, no, 0, acc0, acc1);
         for (int t = 0; t < n_pairs; ++t) {
-          step(second_c, yes, yes, buf(t), 1, acc1, acc0);
+          step(second_c, yes, yes, 1, acc1, acc0);
           tile_ready(t + 1);
-          step(second_c, yes, yes, buf(t + 1), 0, acc0, acc1);
+          other_stage();
+          step(second_c, yes, yes, 0, acc0, acc1);
           if constexpr (kSecond) flush_tile(t);
         }
         // Tile n_pairs: one more plain half when n_plain is odd, then the
         // diagonal half.
         if (n_plain & 1) {
-          step(second_c, yes, yes, buf(n_pairs), 1, acc1, acc0);
+          step(second_c, yes, yes, 1, acc1, acc0);
           mask_diagonal(acc1);
-          step(second_c, no, yes, 0, 0, acc0, acc1);
+          step(second_c, no, yes, 0, acc0, acc1);
         } else {
           mask_diagonal(acc0);
-          step(second_c, no, yes, 0, 0, acc1, acc0);
+          step(second_c, no, yes, 0, acc1, acc0);
         }
         if constexpr (kSecond) flush_tile(n_pairs);
       }
       for (int t = (wave_active ? n_pairs : 0) + 1; t < ntiles; ++t) tile_ready(t);
+      // n_pairs changes of stage so far; the next pass begins at stage (cnt + ntiles) & 1.
+      if ((ntiles - n_pairs) & 1) other_stage();
       cnt += ntiles;
     };
 
