@@ -58,6 +58,12 @@ __global__ void __launch_bounds__(INW * 64, 2) influence_kernel(InfluenceArgs a)
   constexpr int CPR = RB / 16;            // 16-byte chunks per row
   constexpr int TILE = IBN * RB;          // one K or V tile (rows unpadded)
   constexpr int DPW = TILE / 1024 / INW;  // 1 KB direct-to-LDS loads per wave per tile
+  // At head_dim 128 one tile load follows each pair of products: issued together
+  // after the barrier, a work-group's 32 loads queue for the compute unit's
+  // address unit (2 x 32 heads x 4,096: 564 -> 553 us, 16 heads x 1,501: 52.2 ->
+  // 49.6).  At head_dim 64 there are 16 and they stay together (16 heads x 700:
+  // 20.2 us, spread 21.2; 2 x 32 heads x 4,096 the same).
+  constexpr bool kSpread = D == 128;
 
   // K stages 0 and 1, then V stages 0 and 1: one lane address serves all
   // operand reads of a head-dimension step, the rest are instruction offsets.
@@ -107,18 +113,26 @@ __global__ void __launch_bounds__(INW * 64, 2) influence_kernel(InfluenceArgs a)
   // visible).
   const uint32_t last_row = uint32_t(n - 1) * kv_row_bytes;
   const uint32_t span = last_row + RB;
-  auto issue = [&](int b, int it, int buf) {
+  struct Loads {                                  // the next tile's
+    i32x4 kd, vd;
+    uint32_t tile_off;
+    int stage;
+  };
+  auto loads_of = [&](int b, int it, int buf) {
     const int64_t first = int64_t(b) * n * a.hkv + g;             // row 0 of head g, in rows of D
-    const i32x4 kd = make_desc(static_cast<const char*>(a.k) + first * RB, span);
-    const i32x4 vd = make_desc(static_cast<const char*>(a.v) + first * RB, span);
-    const uint32_t tile_off = uint32_t(it * IBN) * kv_row_bytes;
+    return Loads{make_desc(static_cast<const char*>(a.k) + first * RB, span),
+                 make_desc(static_cast<const char*>(a.v) + first * RB, span), uint32_t(it * IBN) * kv_row_bytes, buf};
+  };
+  auto issue_one = [&](const Loads& x, int m) {   // load m: K's DPW, then V's
+    const int i = m % DPW;
+    const uint32_t row_off = src_off + (x.tile_off + uint32_t(i * (64 / CPR)) * kv_row_bytes);
+    const uint32_t off = min(row_off, last_row) + chunk_off[i];
+    dma16_async(m < DPW ? x.kd : x.vd, off,
+                sKV + ((m < DPW ? 0 : 2) + x.stage) * TILE + (wave * DPW + i) * 1024);
+  };
+  auto issue = [&](const Loads& x) {
 #pragma unroll
-    for (int i = 0; i < DPW; ++i) {
-      const uint32_t row_off = src_off + (tile_off + uint32_t(i * (64 / CPR)) * kv_row_bytes);
-      const uint32_t off = min(row_off, last_row) + chunk_off[i];
-      dma16_async(kd, off, sKV + buf * TILE + (wave * DPW + i) * 1024);
-      dma16_async(vd, off, sKV + (2 + buf) * TILE + (wave * DPW + i) * 1024);
-    }
+    for (int m = 0; m < 2 * DPW; ++m) issue_one(x, m);
   };
   // The vector unit bounds the kernel, so addresses are kept, not formed: a pass
   // over a tile took 37 integer adds and 8 quarter-rate products of its 206 - 253
@@ -214,7 +228,7 @@ __global__ void __launch_bounds__(INW * 64, 2) influence_kernel(InfluenceArgs a)
         df[kk] = bf16x8{};
       }
     }
-    if (b == 0) issue(b, 0, cnt & 1);       // later items' first tiles come with the previous pass
+    if (b == 0) issue(loads_of(b, 0, cnt & 1));       // later items' first tiles come with the previous pass
     // Q / dO are waited for here, once: the tile loads are invisible to the
     // compiler's wait tracking, which would otherwise wait inside the loop.
     __builtin_amdgcn_s_waitcnt(0x0F70);   // vmcnt(0)
@@ -228,7 +242,8 @@ __global__ void __launch_bounds__(INW * 64, 2) influence_kernel(InfluenceArgs a)
     // of two groups later from LDS, issues its two MFMAs and then 16 / KS elements of
     // vector work, which run while the matrix core is busy.  The scheduling
     // barrier after each group keeps that order.
-    auto step = [&](auto second_c, auto prod_c, auto work_c, int sub, Acc& out, const Acc& in) {
+    auto step = [&](auto second_c, auto prod_c, auto work_c, int sub, Acc& out, const Acc& in, auto loads_c,
+                    const Loads& next) {
       constexpr bool kSecond = decltype(second_c)::value;
       constexpr bool kProd = decltype(prod_c)::value;
       constexpr bool kWork = decltype(work_c)::value;
@@ -258,6 +273,10 @@ __global__ void __launch_bounds__(INW * 64, 2) influence_kernel(InfluenceArgs a)
           out.s = mma32(kf[kk % 3], qf[kk], out.s);
           out.d = mma32(vf[kk % 3], df[kk], out.d);
         }
+        if constexpr (decltype(loads_c)::value) {
+          static_assert(2 * DPW == KS, "one load per group");
+          issue_one(next, kk);
+        }
         if constexpr (kWork) {
 #pragma unroll
           for (int e = 0; e < EPG; ++e) {
@@ -279,6 +298,7 @@ __global__ void __launch_bounds__(INW * 64, 2) influence_kernel(InfluenceArgs a)
       constexpr bool kSecond = decltype(second_c)::value;
       const std::true_type yes;
       const std::false_type no;
+      const std::bool_constant<kSpread> spread;
       auto buf = [&](int t) { return (cnt + t) & 1; };
       // The load issued after a pass's last tile is tile 0 of the next pass
       // or item (past the last item: this item's tile 0 again, unused), so
@@ -288,32 +308,39 @@ __global__ void __launch_bounds__(INW * 64, 2) influence_kernel(InfluenceArgs a)
         __syncthreads();                      // ... everyone's; tile t - 1's buffer is free
         const bool last = t + 1 >= ntiles;
         const int next_b = (last && kSecond) ? min(b + 1, a.batch - 1) : b;
-        issue(next_b, last ? 0 : t + 1, buf(t + 1));
+        const Loads x = loads_of(next_b, last ? 0 : t + 1, buf(t + 1));
+        if constexpr (!kSpread) issue(x);
+        return x;
       };
       Acc acc0, acc1;
-      tile_ready(0);
-      if (wave_active) {
-        step(second_c, yes, no, 0, acc0, acc1);
+      Loads next = tile_ready(0);
+      if (!wave_active) {
+        if constexpr (kSpread) issue(next);
+      } else {
+        step(second_c, yes, no, 0, acc0, acc1, spread, next);
         for (int t = 0; t < n_pairs; ++t) {
-          step(second_c, yes, yes, 1, acc1, acc0);
-          tile_ready(t + 1);
+          step(second_c, yes, yes, 1, acc1, acc0, no, next);
+          next = tile_ready(t + 1);
           other_stage();
-          step(second_c, yes, yes, 0, acc0, acc1);
+          step(second_c, yes, yes, 0, acc0, acc1, spread, next);
           if constexpr (kSecond) flush_tile(t);
         }
         // Tile n_pairs: one more plain half when n_plain is odd, then the
         // diagonal half.
         if (n_plain & 1) {
-          step(second_c, yes, yes, 1, acc1, acc0);
+          step(second_c, yes, yes, 1, acc1, acc0, no, next);
           mask_diagonal(acc1);
-          step(second_c, no, yes, 0, acc0, acc1);
+          step(second_c, no, yes, 0, acc0, acc1, no, next);
         } else {
           mask_diagonal(acc0);
-          step(second_c, no, yes, 0, acc1, acc0);
+          step(second_c, no, yes, 0, acc1, acc0, no, next);
         }
         if constexpr (kSecond) flush_tile(n_pairs);
       }
-      for (int t = (wave_active ? n_pairs : 0) + 1; t < ntiles; ++t) tile_ready(t);
+      for (int t = (wave_active ? n_pairs : 0) + 1; t < ntiles; ++t) {
+        next = tile_ready(t);
+        if constexpr (kSpread) issue(next);
+      }
       // n_pairs changes of stage so far; the next pass begins at stage (cnt + ntiles) & 1.
       if ((ntiles - n_pairs) & 1) other_stage();
       cnt += ntiles;
