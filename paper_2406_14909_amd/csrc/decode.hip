@@ -90,6 +90,8 @@ __device__ __forceinline__ int64_t div_floor(int64_t a, int64_t b) {
   return q * b > a ? q - 1 : q;
 }
 
+__device__ __forceinline__ int uniform(int x) { return __builtin_amdgcn_readfirstlane(x); }
+
 __device__ __forceinline__ int64_t uniform64(int64_t x) {
   const uint32_t lo = __builtin_amdgcn_readfirstlane(static_cast<int>(x & 0xffffffff));
   const uint32_t hi = __builtin_amdgcn_readfirstlane(static_cast<int>(x >> 32));
@@ -98,14 +100,17 @@ __device__ __forceinline__ int64_t uniform64(int64_t x) {
 
 // The worker whose piece holds virtual key x.
 __device__ __forceinline__ int worker_of(const DecodeArgs& a, int64_t x) {
-  return __builtin_amdgcn_readfirstlane(static_cast<int>(div_floor(x, a.per_worker)));
+  return uniform(static_cast<int>(div_floor(x, a.per_worker)));
 }
 
 // Filled slots of KV head g in sequence b; 0 for an idle sequence (negative
-// position).
+// position).  Only per-sequence positions are read from memory: a choice between
+// two addresses would become a vector load, waited for before each cache's first
+// row (about 1 us per call).
 __device__ __forceinline__ int cache_fill(const DecodeArgs& a, int b, int g) {
-  const int last = a.positions == nullptr ? a.last : a.positions[b];
-  return last < 0 ? 0 : min(last, a.capacity[g] - 1) + 1;
+  if (a.positions == nullptr) return a.limit[g];
+  const int last = uniform(a.positions[b]);
+  return last < 0 ? 0 : min(last, a.limit[g] - 1) + 1;
 }
 
 // Calls seg(b, g, lo, hi, whole) for each cache that worker w's piece touches:
@@ -113,20 +118,21 @@ __device__ __forceinline__ int cache_fill(const DecodeArgs& a, int b, int g) {
 // covers the cache's entire virtual segment.  Work-group uniform.
 template <class Seg>
 __device__ __forceinline__ void for_each_segment(const DecodeArgs& a, int w, Seg&& seg) {
+  // All segment ends at once (a search entry by entry would be a chain of
+  // dependent reads of the kernel arguments), on their way while the piece is
+  // found; lanes past the last head hold the end of the sequence, which r is below.
+  const int64_t seg_end = a.seg_start[min(static_cast<int>(threadIdx.x & 63) + 1, a.hkv)];
   int64_t x = int64_t(w) * a.per_worker;
   const int64_t x_end = uniform64(min(a.total, x + a.per_worker));
   if (x >= x_end) return;
-  int b = __builtin_amdgcn_readfirstlane(static_cast<int>(div_floor(x, a.seq_keys)));
+  int b = uniform(static_cast<int>(div_floor(x, a.seq_keys)));
   int64_t r = x - int64_t(b) * a.seq_keys;
-  // All segment ends at once: a search entry by entry would be a chain of
-  // dependent reads of the kernel arguments.
-  const int lane = threadIdx.x & 63;
-  int g = __builtin_popcountll(__ballot(lane < a.hkv && a.seg_start[lane + 1] <= r));
+  int g = __builtin_popcountll(__ballot(seg_end <= r));
   while (x < x_end) {
     const int64_t s0 = a.seg_start[g];
     const int len = static_cast<int>(a.seg_start[g + 1] - s0);
     const int lo = static_cast<int>(r - s0);
-    const int hi = __builtin_amdgcn_readfirstlane(static_cast<int>(min(int64_t(len), int64_t(lo) + (x_end - x))));
+    const int hi = uniform(static_cast<int>(min(int64_t(len), int64_t(lo) + (x_end - x))));
     seg(b, g, lo, hi, lo == 0 && hi == len);
     x += hi - lo;
     r += hi - lo;
@@ -562,11 +568,10 @@ __global__ void __launch_bounds__(256) decode_combine_kernel(DecodeArgs a) {
   const int bg = static_cast<int>(blockIdx.x) / (G / HS);
   const int h0 = (static_cast<int>(blockIdx.x) - bg * (G / HS)) * HS;   // first head of the slice
   const int b = bg / a.hkv, g = bg - b * a.hkv;
-  if (cache_fill(a, b, g) == 0) return;
   const int64_t base = int64_t(b) * a.seq_keys + a.seg_start[g];
   const int64_t len = a.seg_start[g + 1] - a.seg_start[g];
   const int w0 = worker_of(a, base), w1 = worker_of(a, base + len - 1);
-  if (w0 == w1) return;                       // written directly by its worker
+  if (w0 == w1 || cache_fill(a, b, g) == 0) return;   // written directly by its worker, or idle
   const int np = w1 - w0 + 1;
   const int pg = static_cast<int>(threadIdx.x) / TPR, j = static_cast<int>(threadIdx.x) % TPR;
   const int h = j / V4, d4 = j % V4;

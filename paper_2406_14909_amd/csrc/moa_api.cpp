@@ -49,7 +49,7 @@ static moa_status_t decode_args(const moa_plan_s& p, const char* who, const void
   a->seg_start[0] = 0;
   for (int h = 0; h < d.num_kv_heads; ++h) {
     a->seg_start[h + 1] = a->seg_start[h] + seg_len[h];
-    a->capacity[h] = p.capacity[h];
+    a->limit[h] = static_cast<int32_t>(seg_len[h]);
     a->offset[h] = p.offset[h];
   }
   a->seq_keys = a->seg_start[d.num_kv_heads];
@@ -330,7 +330,6 @@ moa_status_t moa_decode(const moa_plan_t* plan, const void* q, const void* k_cac
   DecodeArgs a;
   const moa_status_t st = decode_args(*plan, "moa_decode", q, k_cache, v_cache, o, batch, workspace, seg_len, &a);
   if (st != MOA_OK) return st;
-  a.last = static_cast<int32_t>(pos);
   const int err = launch_decode(a, d.dtype, d.head_dim, plan->group, hip_stream);
   if (err) return fail(MOA_ERR_HIP, "moa_decode: kernel launch failed (hipError " + std::to_string(err) + ")");
   return ok();
@@ -363,7 +362,6 @@ moa_status_t moa_decode_noalloc(const moa_plan_t* plan, const void* q, const voi
   DecodeArgs a;
   const moa_status_t st = decode_args(*plan, "moa_decode_noalloc", q, k_cache, v_cache, o, batch, ws, seg_len, &a);
   if (st != MOA_OK) return st;
-  a.last = static_cast<int32_t>(pos);
   const int err = launch_decode(a, d.dtype, d.head_dim, plan->group, hip_stream);
   if (err) return fail(MOA_ERR_HIP, "moa_decode_noalloc: kernel launch failed (hipError " + std::to_string(err) + ")");
   return ok();

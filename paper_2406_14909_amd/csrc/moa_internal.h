@@ -88,13 +88,12 @@ struct DecodeArgs {
   int64_t seq_keys;          // virtual keys per sequence (= seg_start[hkv])
   int64_t per_worker;        // ceil(total / workers) (set by the launcher)
   int32_t workers;           // set by the launcher
-  int32_t last;              // position of every sequence, where positions is null
   int32_t batch;
   int32_t hq;
   int32_t hkv;
   float scale_log2;
   int64_t seg_start[MOA_MAX_KV_HEADS + 1];
-  int32_t capacity[MOA_MAX_KV_HEADS];
+  int32_t limit[MOA_MAX_KV_HEADS];   // filled slots of every sequence; with positions the capacity
   int64_t offset[MOA_MAX_KV_HEADS];
 };
 

@@ -8,6 +8,9 @@ library's own flags (no GPU needed).
 * Each lane swap (``v_permlane16_swap`` / ``v_permlane32_swap``, also inline
   asm) follows at least 2 wait states (``s_nop 1`` or longer), the count the
   compiler itself puts between a vector-ALU write and such a swap.
+* No flat loads or stores: a load that may go to two kinds of memory is waited
+  for with everything else in flight (a choice between a kernel argument and a
+  device array once became one, before every cache of a decode call).
 * No packed fp32 VALU forms are emitted (they are kept out of every kernel by
   the build flags).
 """
@@ -75,3 +78,9 @@ def test_no_packed_fp32_forms(src, device_asm):
     asm = device_asm(src)
     found = sorted(set(re.findall(r"\bv_pk_(?:add|mul|fma|mov)_f32\b", asm)))
     assert not found, f"{src}: packed fp32 forms {found}"
+
+
+@pytest.mark.parametrize("src", B.HIP_SOURCES)
+def test_no_flat_memory_access(src, device_asm):
+    found = [t for t in _instructions(device_asm(src)) if re.match(r"flat_(load|store|atomic)", t)]
+    assert not found, f"{src}: {len(found)} flat accesses, first {found[0]!r}"
