@@ -11,8 +11,8 @@
 // heads, so the work is not cut per cache: all filled slots of the batch,
 // laid end to end in (sequence, KV head) order, form one virtual key range
 // that is cut into equal pieces, one per work-group ("worker"), with at most
-// as many workers as the chip holds resident work-groups.  A worker walks its piece
-// cache by cache; its 4 waves take interleaved rows (or tiles) of each cache
+// as many workers as the chip holds resident work-groups (decode_split.h).  A
+// worker walks its piece cache by cache; its 4 waves take interleaved rows (or tiles) of each cache
 // and keep an online softmax (base 2, running max m, running sum l,
 // unnormalised output acc) for all G query heads of the KV head, so each K/V
 // byte is read from HBM once; the waves' states are merged through LDS at the
@@ -42,6 +42,7 @@
 #include <atomic>
 #include <mutex>
 
+#include "decode_split.h"
 #include "moa_device.h"
 
 namespace moa {
@@ -83,24 +84,12 @@ constexpr int kWaves = 4;          // waves per worker (work-group)
 template <int G>
 constexpr int mma_keys() { return 32; }
 
-// a / b for 0 <= a < 2^53, b > 0 (the fp64 quotient is never below the floor;
-// a 64-bit integer division is a chain of several hundred cycles).
-__device__ __forceinline__ int64_t div_floor(int64_t a, int64_t b) {
-  const int64_t q = static_cast<int64_t>(static_cast<double>(a) / static_cast<double>(b));
-  return q * b > a ? q - 1 : q;
-}
-
 __device__ __forceinline__ int uniform(int x) { return __builtin_amdgcn_readfirstlane(x); }
 
 __device__ __forceinline__ int64_t uniform64(int64_t x) {
   const uint32_t lo = __builtin_amdgcn_readfirstlane(static_cast<int>(x & 0xffffffff));
   const uint32_t hi = __builtin_amdgcn_readfirstlane(static_cast<int>(x >> 32));
   return static_cast<int64_t>((uint64_t(hi) << 32) | lo);
-}
-
-// The worker whose piece holds virtual key x.
-__device__ __forceinline__ int worker_of(const DecodeArgs& a, int64_t x) {
-  return uniform(static_cast<int>(div_floor(x, a.per_worker)));
 }
 
 // Filled slots of KV head g in sequence b; 0 for an idle sequence (negative
@@ -122,10 +111,9 @@ __device__ __forceinline__ void for_each_segment(const DecodeArgs& a, int w, Seg
   // dependent reads of the kernel arguments), on their way while the piece is
   // found; lanes past the last head hold the end of the sequence, which r is below.
   const int64_t seg_end = a.seg_start[min(static_cast<int>(threadIdx.x & 63) + 1, a.hkv)];
-  int64_t x = int64_t(w) * a.per_worker;
-  const int64_t x_end = uniform64(min(a.total, x + a.per_worker));
-  if (x >= x_end) return;
-  int b = uniform(static_cast<int>(div_floor(x, a.seq_keys)));
+  int64_t x = uniform64(worker_start(a, w));
+  const int64_t x_end = uniform64(worker_start(a, w + 1));
+  int b = uniform(static_cast<int>(mul_floor(x, a.inv_seq_keys)));
   int64_t r = x - int64_t(b) * a.seq_keys;
   int g = __builtin_popcountll(__ballot(seg_end <= r));
   while (x < x_end) {
@@ -546,8 +534,9 @@ __global__ void __launch_bounds__(kWaves * 64, mma_keys<G>() == 32 ? 3 : 2) deco
 // workers w0..w1 sit at consecutive slots w0 + cache .. w1 + cache.  Thread
 // groups of TPR threads (one float4 of each of the slice's head rows) take
 // every PG-th partial, MD of them in flight, keep an online merge of their own
-// and meet in LDS.  All bound by latency: one trip for the partials.  The loads
-// are unconditional with the partial's number clamped: a branch per load, as an
+// and meet in LDS.  All bound by latency: one trip to memory per PG * MD partials
+// (16 with two heads per slice at head_dim 128, 32 with one).  The loads are
+// unconditional with the partial's number clamped: a branch per load, as an
 // earlier version had, makes a chain of them once the compiler knows the number
 // of partials to be uniform (10 us instead of 4).
 // ---------------------------------------------------------------------------
@@ -570,7 +559,7 @@ __global__ void __launch_bounds__(256) decode_combine_kernel(DecodeArgs a) {
   const int b = bg / a.hkv, g = bg - b * a.hkv;
   const int64_t base = int64_t(b) * a.seq_keys + a.seg_start[g];
   const int64_t len = a.seg_start[g + 1] - a.seg_start[g];
-  const int w0 = worker_of(a, base), w1 = worker_of(a, base + len - 1);
+  const int w0 = uniform(worker_of(a, base)), w1 = uniform(worker_of(a, base + len - 1));
   if (w0 == w1 || cache_fill(a, b, g) == 0) return;   // written directly by its worker, or idle
   const int np = w1 - w0 + 1;
   const int pg = static_cast<int>(threadIdx.x) / TPR, j = static_cast<int>(threadIdx.x) % TPR;
@@ -644,9 +633,6 @@ int resident_groups(const void* kernel, std::atomic<int>* cache) {
   return groups;
 }
 
-constexpr int64_t kMaxParts = 64;      // partials per cache in a call of short pieces
-constexpr int64_t kRoundedMax = 16;    // rounds per worker up to which pieces are whole rounds
-
 template <typename T, int D, int G>
 int launch_t(DecodeArgs a, void* stream) {
   constexpr bool kMma = sizeof(T) == 2 && G >= 2;
@@ -657,43 +643,13 @@ int launch_t(DecodeArgs a, void* stream) {
   else kernel = reinterpret_cast<const void*>(&decode_valu_kernel<T, D, G>);
   static std::atomic<int> group_cache[64];
   const int64_t slots = std::min<int64_t>(resident_groups(kernel, group_cache), kMaxDecodeWorkers);
-  // Short pieces are cut in whole rounds, each cache starting a new one: a
-  // piece of 257 keys where a round holds 128 takes three rounds, not two, and
-  // in a small call a round is a chain of about 3 us.  One round per worker is
-  // the fastest as long as the slots last and no cache has more than
-  // kMaxParts partials for the merge to read (per call: 32 heads of 1,064 keys
-  // on average 14.1 -> 8.1 us, of 2,112 keys 15.1 -> 12.5; 8 KV heads x 8 query
-  // heads of 2,112 keys 14.6 -> 9.9; 4 query heads, 8,256 keys, where the
-  // limit decides: 17.7 -> 15.7, without it 19.5).  From kRoundedMax rounds on
-  // the last, partial round weighs little and equal pieces fill the slots
-  // better.
-  int64_t rounds = 0, longest = 0;
-  for (int g = 0; g < a.hkv; ++g) {
-    const int64_t n = (a.seg_start[g + 1] - a.seg_start[g] + kRound - 1) / kRound;
-    rounds += n;
-    longest = std::max(longest, n);
-  }
-  const int64_t k = std::max((rounds * a.batch + slots - 1) / slots, (longest + kMaxParts - 1) / kMaxParts);
-  if (k <= kRoundedMax) {
-    int64_t at = 0, prev = 0;
-    for (int g = 0; g < a.hkv; ++g) {
-      const int64_t end = a.seg_start[g + 1];
-      at += (end - prev + kRound - 1) / kRound * kRound;
-      prev = end;
-      a.seg_start[g + 1] = at;
-    }
-    a.seq_keys = at;
-    a.total = at * a.batch;
-    a.per_worker = k * kRound;
-  } else {
-    a.per_worker = (a.total + slots - 1) / slots;
-  }
-  const int64_t workers = (a.total + a.per_worker - 1) / a.per_worker;
-  a.workers = static_cast<int32_t>(workers);
+  constexpr int kRoundShift = __builtin_ctz(kRound);
+  static_assert(kRound == 1 << kRoundShift, "rounds of a power of two keys");
+  split_decode(a, slots, kRoundShift, kMma);
   void* args[] = {&a};
-  hipError_t e = hipLaunchKernel(kernel, dim3(static_cast<unsigned>(workers)), dim3(kWaves * 64), args, 0,
+  hipError_t e = hipLaunchKernel(kernel, dim3(static_cast<unsigned>(a.workers)), dim3(kWaves * 64), args, 0,
                                  static_cast<hipStream_t>(stream));
-  if (e != hipSuccess || workers == 1) return static_cast<int>(e);   // one worker: every cache is whole
+  if (e != hipSuccess || a.workers == 1) return static_cast<int>(e);   // one worker: every cache is whole
   e = hipLaunchKernel(reinterpret_cast<const void*>(&decode_combine_kernel<T, D, G>),
                       dim3(static_cast<unsigned>(a.batch * a.hkv * (G / merge_heads<G>()))), dim3(256), args, 0,
                       static_cast<hipStream_t>(stream));

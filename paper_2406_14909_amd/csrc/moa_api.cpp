@@ -9,6 +9,7 @@
 #include <numeric>
 #include <string>
 
+#include "decode_split.h"
 #include "moa_internal.h"
 
 namespace moa {
@@ -53,10 +54,9 @@ static moa_status_t decode_args(const moa_plan_s& p, const char* who, const void
     a->offset[h] = p.offset[h];
   }
   a->seq_keys = a->seg_start[d.num_kv_heads];
-  if (a->seq_keys <= 0 || static_cast<double>(a->seq_keys) * batch >= 9007199254740992.0 ||
+  if (a->seq_keys <= 0 || static_cast<double>(a->seq_keys) * batch >= static_cast<double>(kMaxVirtual) ||
       static_cast<int64_t>(batch) * d.num_kv_heads >= (int64_t(1) << 31))
     return fail(MOA_ERR_UNSUPPORTED, std::string(who) + ": batch x cache slots too large for one launch");
-  a->total = a->seq_keys * batch;
   return ok();
 }
 

@@ -73,8 +73,8 @@ struct AppendArgs {
 
 // Decode work split: the filled cache slots of every (sequence, KV head) pair,
 // laid end to end in (sequence, head) order, form one virtual key range of
-// `total` keys, cut into equal pieces (one per work-group): worker w covers
-// [w * per_worker, (w + 1) * per_worker).  Head g of a sequence owns
+// batch * seq_keys keys, cut into one piece per work-group ("worker"), counted
+// in units of 2^unit_shift keys (decode_split.h).  Head g of a sequence owns
 // virtual keys [seg_start[g], seg_start[g + 1]) of that sequence's range.
 struct DecodeArgs {
   const void* q;
@@ -84,10 +84,18 @@ struct DecodeArgs {
   float* part;               // [workers + batch * hkv][group][head_dim + 4] partials
   const int32_t* positions;  // per-sequence positions (device), or null: one position for all
   int64_t rows_total;        // cache rows per sequence
-  int64_t total;             // virtual keys = batch * seq_keys (the launcher may round each head's up)
-  int64_t seq_keys;          // virtual keys per sequence (= seg_start[hkv])
-  int64_t per_worker;        // ceil(total / workers) (set by the launcher)
-  int32_t workers;           // set by the launcher
+  int64_t seq_keys;          // virtual keys per sequence (= seg_start[hkv]; the launcher may round each head's up)
+  int64_t units;             // units in all (from here to unit_shift: set by the launcher)
+  int64_t per_worker;        // units / workers
+  double inv_workers;        // 1 / workers
+  double inv_seq_keys;       // 1 / seq_keys
+  int32_t rem;               // units % workers
+  int32_t workers;
+  int32_t unit_shift;        // log2 of the virtual keys per unit
+  int32_t first_mul;         // these four: for worker_of
+  int64_t first_units;
+  double inv_first;
+  double inv_later;
   int32_t batch;
   int32_t hq;
   int32_t hkv;

@@ -23,6 +23,8 @@ CASES = [
     ("bf16", 4, 2, 64, 1, 64, (64, 65), 127),
     ("bf16", 32, 32, 128, 16, 0, tuple(range(4000, 4320, 10)), 5000),   # pieces of many rounds
     ("bf16", 32, 4, 64, 24, 3, (5000, 3, 1021, 2045), 7000),
+    ("bf16", 16, 8, 128, 4, 0, (3072,) * 7 + (3073,), 5000),            # a little over a round per slot: two each
+    ("bf16", 64, 8, 128, 8, 4, (4090, 4093) * 4, 5000),                 # over two: equal numbers of keys
 ]
 
 
