@@ -6,11 +6,12 @@
 // both are "j >= band_start(i)" with band_start(i) = ((i >> sh) - W + 1) << sh.
 //
 // One work-group = 4 waves = 128 query rows of one (sequence, query head) in a
-// large launch (small ones: launch_d below); each wave owns 32 rows.  The work-group walks only the 64-key tiles that
-// intersect the sink prefix or the band of its rows; every other tile is
-// skipped without being read.  K and V tiles are staged in LDS (the global
-// loads of the next tiles are in flight while a tile is computed, one barrier
-// per tile) and shared by the 4 waves.  fp32 plans have a kernel of their own.
+// large launch (small ones: prefill_rule.h); each wave owns 32 rows.  The
+// work-group walks only the 64-key tiles that intersect the sink prefix or the
+// band of its rows; every other tile is skipped without being read.  K and V
+// tiles are staged in LDS (the global loads of the next tiles are in flight
+// while a tile is computed, one barrier per tile) and shared by the 4 waves.
+// fp32 plans have a kernel of their own.
 //
 // Matrix-core formulation (CDNA4 32x32x16 bf16 MFMA):
 //   S^T = K Q^T  : A = K tile rows (keys), B = Q^T kept in registers.
@@ -35,6 +36,7 @@
 #include <type_traits>
 
 #include "moa_device.h"
+#include "prefill_rule.h"
 
 namespace moa {
 
@@ -541,46 +543,22 @@ __global__ void __launch_bounds__(NR * KG * 64, D == 128 && NR * KG == 4 && KG >
 template <int D, int NR, int KG>
 int launch_t(const PrefillArgs& a, void* stream) {
   PrefillArgs copy = a;
-  // A unit spans at least kPrefillUnitBlocks work-groups (query tiles x group),
-  // and at least kPrefillChunk query tiles.
-  const int64_t tiles = (a.n + 32 * NR - 1) / (32 * NR);
-  const int64_t qchunk = std::min<int64_t>(std::max<int64_t>(kPrefillChunk, kPrefillUnitBlocks / a.group), tiles);
-  const int64_t n_chunks = (tiles + qchunk - 1) / qchunk;
-  const int64_t n_units = int64_t(a.hkv) * a.batch * n_chunks;
-  const int64_t blocks = (n_units + kNumXcd - 1) / kNumXcd * kNumXcd * a.group * qchunk;
-  copy.n_qtiles = static_cast<int32_t>(tiles);
-  copy.qchunk = static_cast<int32_t>(qchunk);
-  copy.n_chunks = static_cast<int32_t>(n_chunks);
-  copy.n_units = static_cast<int32_t>(n_units);
+  const PrefillGrid g = prefill_grid(a, 32 * NR);
+  copy.n_qtiles = static_cast<int32_t>(g.tiles);
+  copy.qchunk = static_cast<int32_t>(g.qchunk);
+  copy.n_chunks = static_cast<int32_t>(g.n_chunks);
+  copy.n_units = static_cast<int32_t>(g.n_units);
   void* args[] = {&copy};
   return static_cast<int>(hipLaunchKernel(reinterpret_cast<const void*>(&prefill_kernel<D, NR, KG>),
-                                          dim3(static_cast<unsigned>(blocks)), dim3(NR * KG * 64), args, 0,
+                                          dim3(static_cast<unsigned>(g.blocks)), dim3(NR * KG * 64), args, 0,
                                           static_cast<hipStream_t>(stream)));
 }
 
-// A launch of few work-groups takes as long as its longest chain of tiles (a
-// tile of a lone work-group 1.65 us at head_dim 128, of two on a compute unit
-// 1.9), so the chain is split over two key groups, where each work-group has a
-// compute unit (head_dim 128: 160 KB of LDS) to itself:
-//   64 rows per work-group as long as those fit the chip at once: 32 heads x 512
-//     18.6 -> 15.0 us, x 256 11.7 -> 10.3; head_dim 64, 16 heads x 512 13.8 -> 9.7,
-//     32 heads x 1,024 23.2 -> 16.1;
-//   128 rows then: 32 heads x 1,024 30.6 -> 26.1, and, where every compute unit
-//     gets two of them in turn, only for long chains: 32 heads x 2,048 57.0 ->
-//     54.6, 16 heads x 3,000 94.6 -> 61.6, but 2 x 32 heads x 1,024 33.6 -> 38.9.
-// With more work-groups two per compute unit cover each other's waits and their
-// starts and ends (32 heads x 4,096: 128 us against 139).
 template <int D>
 int launch_d(const PrefillArgs& a, void* stream) {
-  const int64_t heads = int64_t(a.batch) * a.hq;
-  const int64_t w64 = (a.n + 63) / 64 * heads, w128 = (a.n + 127) / 128 * heads;
-  int64_t widest = 0;
-  for (int g = 0; g < a.hkv; ++g) widest = std::max(widest, int64_t(a.window[g]) << a.band_shift);
-  const int64_t chain = std::min((a.n + BN - 1) / BN, (a.num_sink + BN - 1) / BN + widest / BN + 3);
-  constexpr int64_t kFit64 = D == 128 ? 256 : 512;      // work-groups of 160 (80) KB of LDS on the chip
-  constexpr int64_t kLong = D == 128 ? 20 : 12;
-  if (w64 <= kFit64 && chain >= 3) return launch_t<D, 2, 2>(a, stream);
-  if ((w128 <= 256 && chain >= 6) || (w128 <= 512 && chain >= kLong)) return launch_t<D, 4, 2>(a, stream);
+  const PrefillShape shape = prefill_shape(a, D);
+  if (shape.waves == 2) return launch_t<D, 2, 2>(a, stream);
+  if (shape.key_groups == 2) return launch_t<D, 4, 2>(a, stream);
   return launch_t<D, 4, 1>(a, stream);
 }
 

@@ -79,6 +79,10 @@ def test_prefill_f32_window_of_one_key_is_exact():
     # 128 rows, two key groups
     (1, 32, 32, 128, 513, 0, 0), (1, 32, 8, 128, 1024, 64, M.MOA_BLOCK_BAND), (1, 16, 2, 128, 3001, 1, 0),
     (4, 16, 16, 64, 1000, 4, 0), (1, 16, 16, 64, 4033, 64, 0),
+    # few (KV head, sequence) pairs, whose work-groups share a die: 128 rows and one key group, or, with long or few
+    # chains, as above
+    (1, 8, 1, 128, 1024, 4, 0), (1, 16, 2, 128, 777, 64, 0), (1, 8, 1, 64, 1024, 4, 0), (1, 8, 1, 64, 4096, 4, 0),
+    (1, 16, 2, 64, 3000, 64, 0), (1, 4, 4, 128, 193, 0, 0), (1, 4, 1, 128, 1500, 4, 0),
     # two work-groups of 128 rows per compute unit and more
     (2, 32, 32, 128, 1025, 4, 0), (5, 16, 4, 64, 1000, 0, M.MOA_BLOCK_BAND),
 ])
