@@ -1,5 +1,5 @@
-// Grid of a bf16 prefill launch and the choice of its kernel.  Plain C++, so that
-// it also compiles without a GPU toolchain.
+// Grids of prefill launches and the choice of their kernels.  Plain C++, so that it
+// also compiles without a GPU toolchain.
 #pragma once
 
 #include <stdint.h>
@@ -30,7 +30,7 @@ inline PrefillGrid prefill_grid(const PrefillArgs& a, int rows) {
   return g;
 }
 
-// Waves of 32 query rows and key groups per work-group.
+// Waves of 32 query rows and key groups per work-group of a bf16 launch.
 struct PrefillShape {
   int waves, key_groups;
 };
@@ -77,6 +77,57 @@ inline PrefillShape prefill_shape(const PrefillArgs& a, int head_dim) {
   const int64_t all128 = (a.n + 127) / 128 * a.batch * a.hq;
   if (uneven && d128 <= 4 * kUnits && all128 <= 2 * kUnits * kNumXcd) return {4, 2};
   return {4, 1};
+}
+
+// Kernel of an fp32 launch: 64-key tiles shared through LDS, or a wave's operands
+// straight from memory, with 32 or 64 rows per wave and 1, 2 or 4 waves per block
+// of rows.
+struct PrefillF32Shape {
+  bool shared;
+  int key_groups, row_blocks;
+};
+
+// Blocks of 32 rows decide how many waves share one.  head_dim 128 (one wave per
+// SIMD: 370 registers): 504 blocks 366 us with shared tiles, 93 with 4 waves per
+// block (2: 142); 1,024 blocks 193, 95 with 2 (4: 114); 4,096 blocks 817, 546
+// with one (2: 560).
+//
+// head_dim 64, lines drawn through 288 launches of 4 to 256 heads, 700 to 16,384
+// tokens and windows of 0.2 to 1.0 of them, each with every kernel (us: shared
+// tiles, 4 waves per 32 rows, 4 waves per 64, 2 waves per 64):
+//   few blocks: 8 heads x 1,501 125, 49, -, 57; 32 heads x 2,048 292, 203, 208, 279.
+//   from 2,900 blocks on a wave takes 64 rows, which halves its loads per product:
+//     128 heads x 1,024 293, 207, 199, 214; 32 heads x 4,096 849, 786, 705, 739.
+//   shared tiles where K and V are read many times over, that is for long prompts,
+//     the sooner the more query heads share a KV head, and need fewer operand loads
+//     still: 64 query and 8 KV heads x 2,500 on, 32 and 8 x 3,500 on, 32 and 32 x
+//     5,000 on (64 and 8 x 8,192 4,557, 6,098, 5,332, 5,361; 32 and 8 x 8,192
+//     2,319, 2,949, 2,671, 2,703), with few heads only
+//     where the windows are narrow (8 heads x 8,192, windows of 1,638 268, 296, 293, 308).  They
+//     keep a (KV head, sequence) pair on one die: with less than 4 pairs not, nor
+//     with windows so short that little is read twice (32 and 8 x 4,096, windows of
+//     81: 103, -, -, 90).
+//   2 waves per 64 rows where a launch of narrow windows then has one work-group
+//     for every compute unit (32 heads x 1,024, windows of 204 39, 41, 43, 31), and
+//     where windows have few tiles to share out (128 heads x 2,048, windows of 40 173,
+//     -, 166, 145).
+inline PrefillF32Shape prefill_f32_shape(const PrefillArgs& a, int head_dim) {
+  const int64_t blocks = (a.n + 31) / 32 * a.batch * a.hq;
+  if (head_dim == 128) return {false, blocks >= 2500 ? 1 : blocks >= 800 ? 2 : 4, 1};
+  int64_t widest = 0;
+  for (int g = 0; g < a.hkv; ++g) widest = std::max(widest, int64_t(a.window[g]) << a.band_shift);
+  const int64_t span = std::min(a.n, a.num_sink + widest), pairs = int64_t(a.hkv) * a.batch;
+  const bool narrow = 3 * span < a.n, wide = 4 * span >= 3 * a.n;
+  const int64_t long_n = a.group >= 8 ? 2500 : a.group >= 4 ? 3500 : 5000;
+  const bool reread = pairs >= 4 && span >= 512;
+  if (reread && blocks >= 3000 &&
+      (a.n >= long_n || (a.n >= 3500 && blocks >= 16000) || (a.n >= 1400 && a.group >= 8 && wide)))
+    return {true, 1, 1};
+  if (reread && blocks >= 2000 && a.n >= 8000 && narrow) return {true, 1, 1};
+  if (pairs >= 2 && span >= 512 && blocks >= 8000 && a.n >= 14000) return {true, 1, 1};
+  if (narrow && blocks >= 850 && blocks <= 1024) return {false, 2, 2};
+  if (blocks < 2900) return {false, 4, 1};
+  return {false, span < 256 ? 2 : 4, 2};
 }
 
 }  // namespace moa

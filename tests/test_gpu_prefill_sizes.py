@@ -60,9 +60,21 @@ def test_prefill_f32_sizes(b, hq, hkv, d, n, s, flags):
     _run("f32", b, hq, hkv, d, n, s, flags, windows)
 
 
+@pytest.mark.parametrize("b,hq,hkv,n,s,flags,w", [
+    # tiles shared through LDS: last tiles of 1, 63 and 64 keys, and rows that end inside one
+    (1, 64, 8, 2497, 4, 0, 2497), (1, 64, 8, 2559, 64, M.MOA_BLOCK_BAND, 700), (1, 64, 8, 1408, 0, 0, 1408),
+    (1, 32, 8, 3520, 70, 0, 600), (1, 8, 8, 8065, 1, 0, 900),
+    # 64 rows per wave, 2 waves per block
+    (1, 32, 32, 1023, 4, 0, 65), (1, 32, 8, 3520, 70, 0, 64),
+])
+def test_prefill_f32_head_dim_64_long(b, hq, hkv, n, s, flags, w):
+    _run("f32", b, hq, hkv, 64, n, s, flags, [max(1, w - 5 * g) for g in range(hkv)])
+
+
 def test_prefill_f32_window_of_one_key_is_exact():
     """Every path returns v bit for bit where a query sees one key."""
-    for b, h, d, n in ((1, 2, 64, 99), (8, 16, 64, 877), (1, 4, 128, 99), (2, 16, 128, 805), (5, 16, 128, 1000)):
+    for b, h, d, n in ((1, 2, 64, 99), (8, 16, 64, 877), (1, 4, 128, 99), (2, 16, 128, 805), (5, 16, 128, 1000),
+                       (1, 20, 64, 5001)):
         print("[case] prefill one key", b, h, d, n, flush=True)
         plan = M.moa_plan(h, h, d, 0, n, "f32", [1.0] * h, [0.0] * h)
         gen = torch.Generator(device="cuda").manual_seed(n)

@@ -48,6 +48,17 @@ extern "C" int deal(int batch, int hq, int hkv, int head_dim, int64_t n, int win
   out[1] = g.per_die;
   return out[0] <= out[1] ? 0 : 3;
 }
+
+extern "C" void shape_f32(int batch, int hq, int hkv, int head_dim, int64_t n, int window, int* out) {
+  PrefillArgs a;
+  memset(&a, 0, sizeof(a));
+  a.n = n; a.batch = batch; a.hq = hq; a.hkv = hkv; a.group = hq / hkv;
+  for (int g = 0; g < hkv; ++g) a.window[g] = window;
+  const PrefillF32Shape s = prefill_f32_shape(a, head_dim);
+  out[0] = s.shared;
+  out[1] = s.key_groups;
+  out[2] = s.row_blocks;
+}
 """
 
 
@@ -67,6 +78,7 @@ def deal(tmp_path_factory):
         assert st == 0, (st, b, hq, hkv, d, n, window)
         return tuple(shape), res[0]
 
+    call.lib = lib
     return call
 
 
@@ -100,3 +112,24 @@ def test_every_row_tile_once_and_split_work_groups_fit_their_die(deal):
 ])
 def test_shape_at_the_measured_sizes(deal, args, shape):
     assert deal(*args)[0] == shape
+
+
+SHARED, FOUR_32, FOUR_64, TWO_64 = (1, 1, 1), (0, 4, 1), (0, 4, 2), (0, 2, 2)
+
+
+@pytest.mark.parametrize("args,shape", [
+    # long prompts, which the kernels without shared tiles made up to 16 % slower
+    ((1, 64, 8, 64, 8192, 8192), SHARED), ((1, 32, 8, 64, 8192, 4096), SHARED), ((1, 32, 8, 64, 4096, 4096), SHARED),
+    ((1, 32, 32, 64, 8192, 8192), SHARED), ((1, 8, 8, 64, 16384, 16384), SHARED), ((8, 32, 32, 64, 4096, 2048), SHARED),
+    ((1, 8, 8, 64, 8192, 1638), SHARED), ((1, 64, 8, 64, 2048, 2048), SHARED), ((1, 16, 2, 64, 16384, 16384), SHARED),
+    ((1, 8, 8, 64, 8192, 8192), FOUR_32), ((1, 64, 8, 64, 2048, 1024), FOUR_64), ((1, 16, 2, 64, 8192, 8192), FOUR_64),
+    ((1, 32, 32, 64, 4096, 4096), FOUR_64), ((8, 16, 16, 64, 1024, 1024), FOUR_64), ((1, 8, 8, 64, 1501, 1501), FOUR_32),
+    ((1, 32, 32, 64, 2048, 2048), FOUR_32), ((1, 32, 32, 64, 1024, 204), TWO_64), ((1, 1, 1, 64, 1, 1), FOUR_32),
+    ((1, 32, 8, 64, 4096, 81), TWO_64), ((8, 16, 16, 64, 2048, 40), TWO_64),
+    ((1, 32, 32, 128, 4096, 4096), (0, 1, 1)), ((2, 16, 8, 128, 800, 800), (0, 2, 1)), ((1, 4, 4, 128, 99, 1), (0, 4, 1)),
+])
+def test_f32_shape_at_the_measured_sizes(deal, args, shape):
+    out = (ctypes.c_int * 3)()
+    b, hq, hkv, d, n, w = args
+    deal.lib.shape_f32(b, hq, hkv, d, ctypes.c_int64(n), w, out)
+    assert tuple(out) == shape
