@@ -4,10 +4,12 @@
 // binding checks (type, shape, contiguity, device, with the same rules) and
 // makes the call on torch's current stream.  It answers None, having done
 // nothing, wherever anything is out of the ordinary: a wrong shape, another
-// current device, a tensor subclass, an active torch mode, a status other than
-// MOA_OK.  The binding then goes its general way, which accepts or refuses the
-// call with its own messages.  What it saves is host time: about 13 us of
-// interpreted checks per call become about 2.
+// current device, a tensor subclass, an active torch mode.  The binding then goes
+// its general way, which accepts or refuses the call with its own messages.  A
+// call that the library has seen is never made again: a status other than MOA_OK
+// raises the binding's error (after a failed launch part of the work may be
+// enqueued).  What it saves is host time: about 13 us of interpreted checks per
+// call become about 2.
 #include <Python.h>
 
 #include <algorithm>
@@ -46,6 +48,8 @@ struct Bound {
   const moa_plan_t* plan;       // null: for the calls that take no plan
   int64_t hq, hkv, d, rows;
   at::ScalarType dtype;
+  PyObject* check;              // the binding's function that raises for a status
+  ~Bound() { Py_XDECREF(check); }
 };
 constexpr const char* kName = "moa.bound";
 
@@ -91,13 +95,25 @@ struct Check {
   void* stream() const { return c10::hip::getCurrentHIPStream(device).stream(); }
 };
 
+// Makes the call while other Python threads run; false with a Python exception
+// set where it was not MOA_OK.
 template <class F>
-bool call(F&& f) {
-  moa_status_t st;
+bool call(const Bound& b, F&& f) {
+  moa_status_t st = MOA_OK;
+  bool no_memory = false;
   Py_BEGIN_ALLOW_THREADS
-  st = f();
+  try {
+    st = f();
+  } catch (...) {                 // of a message's string: nothing else in the library throws
+    no_memory = true;
+  }
   Py_END_ALLOW_THREADS
-  return st == MOA_OK;
+  if (no_memory) return PyErr_NoMemory(), false;
+  if (st == MOA_OK) return true;
+  PyObject* r = PyObject_CallFunction(b.check, "i", static_cast<int>(st));
+  if (r) PyErr_Format(PyExc_RuntimeError, "moa status %d", static_cast<int>(st));
+  Py_XDECREF(r);
+  return false;
 }
 
 bool as_int(PyObject* o, int64_t* v) {
@@ -154,7 +170,7 @@ PyObject* prefill(PyObject*, PyObject* const* args, Py_ssize_t nargs) {
   Out o(args[4], q, c);
   if (!c.done() || !o.t || bsz > INT32_MAX) return none();
   void *pq = q->data_ptr(), *pk = k->data_ptr(), *pv = v->data_ptr(), *po = o.t->data_ptr(), *s = c.stream();
-  if (!call([&] { return b->api.prefill(b->plan, pq, pk, pv, po, static_cast<int32_t>(bsz), n, s); })) return none();
+  if (!call(*b, [&] { return b->api.prefill(b->plan, pq, pk, pv, po, static_cast<int32_t>(bsz), n, s); })) return nullptr;
   return o.answer();
   MOA_LEAVE
 }
@@ -174,8 +190,8 @@ PyObject* kv_append(PyObject*, PyObject* const* args, Py_ssize_t nargs) {
   if (!c.done() || bsz > INT32_MAX) return none();
   void *pkc = kc->data_ptr(), *pvc = vc->data_ptr(), *pkn = kn->data_ptr(), *pvn = vn->data_ptr(), *s = c.stream();
   int32_t* pp = static_cast<int32_t*>(pc->data_ptr());
-  if (!call([&] { return b->api.kv_append(b->plan, pkc, pvc, pp, pkn, pvn, static_cast<int32_t>(bsz), start, n, s); }))
-    return none();
+  if (!call(*b, [&] { return b->api.kv_append(b->plan, pkc, pvc, pp, pkn, pvn, static_cast<int32_t>(bsz), start, n, s); }))
+    return nullptr;
   Py_RETURN_TRUE;
   MOA_LEAVE
 }
@@ -196,8 +212,8 @@ PyObject* kv_append_ragged(PyObject*, PyObject* const* args, Py_ssize_t nargs) {
   void *pkc = kc->data_ptr(), *pvc = vc->data_ptr(), *pkn = kn->data_ptr(), *pvn = vn->data_ptr(), *s = c.stream();
   int32_t* pp = static_cast<int32_t*>(pc->data_ptr());
   const int32_t* at_ = static_cast<const int32_t*>(ps->data_ptr());
-  if (!call([&] { return b->api.kv_append_ragged(b->plan, pkc, pvc, pp, pkn, pvn, at_, static_cast<int32_t>(bsz), s); }))
-    return none();
+  if (!call(*b, [&] { return b->api.kv_append_ragged(b->plan, pkc, pvc, pp, pkn, pvn, at_, static_cast<int32_t>(bsz), s); }))
+    return nullptr;
   Py_RETURN_TRUE;
   MOA_LEAVE
 }
@@ -231,8 +247,8 @@ PyObject* decode(PyObject*, PyObject* const* args, Py_ssize_t nargs) {
   void *pq = t.q->data_ptr(), *pk = t.kc->data_ptr(), *pv = t.vc->data_ptr(), *po = o.t->data_ptr();
   void *pw = w->data_ptr(), *s = c.stream();
   const size_t nw = w->nbytes();
-  if (!call([&] { return b->api.decode(b->plan, pq, pk, pv, po, static_cast<int32_t>(t.bsz), pos, pw, nw, s); }))
-    return none();
+  if (!call(*b, [&] { return b->api.decode(b->plan, pq, pk, pv, po, static_cast<int32_t>(t.bsz), pos, pw, nw, s); }))
+    return nullptr;
   return o.answer();
   MOA_LEAVE
 }
@@ -246,8 +262,8 @@ PyObject* decode_noalloc(PyObject*, PyObject* const* args, Py_ssize_t nargs) {
   Out o(args[5], t.q, c);
   if (!c.done() || !o.t) return none();
   void *pq = t.q->data_ptr(), *pk = t.kc->data_ptr(), *pv = t.vc->data_ptr(), *po = o.t->data_ptr(), *s = c.stream();
-  if (!call([&] { return b->api.decode_noalloc(b->plan, pq, pk, pv, po, static_cast<int32_t>(t.bsz), pos, s); }))
-    return none();
+  if (!call(*b, [&] { return b->api.decode_noalloc(b->plan, pq, pk, pv, po, static_cast<int32_t>(t.bsz), pos, s); }))
+    return nullptr;
   return o.answer();
   MOA_LEAVE
 }
@@ -264,8 +280,8 @@ PyObject* decode_ragged(PyObject*, PyObject* const* args, Py_ssize_t nargs) {
   void *pw = w->data_ptr(), *s = c.stream();
   const int32_t* at_ = static_cast<const int32_t*>(ps->data_ptr());
   const size_t nw = w->nbytes();
-  if (!call([&] { return b->api.decode_ragged(b->plan, pq, pk, pv, po, at_, static_cast<int32_t>(t.bsz), pw, nw, s); }))
-    return none();
+  if (!call(*b, [&] { return b->api.decode_ragged(b->plan, pq, pk, pv, po, at_, static_cast<int32_t>(t.bsz), pw, nw, s); }))
+    return nullptr;
   return o.answer();
   MOA_LEAVE
 }
@@ -297,7 +313,7 @@ PyObject* influence(PyObject*, PyObject* const* args, Py_ssize_t nargs) {
   desc.softmax_scale = static_cast<float>(PyFloat_AS_DOUBLE(args[6]));
   void *pq = q->data_ptr(), *pk = k->data_ptr(), *pv = v->data_ptr(), *pg = g->data_ptr(), *s = c.stream();
   float* pe = static_cast<float*>(e->data_ptr());
-  if (!call([&] { return b->api.influence(&desc, pq, pk, pv, pg, pe, static_cast<int32_t>(bsz), n, s); })) return none();
+  if (!call(*b, [&] { return b->api.influence(&desc, pq, pk, pv, pg, pe, static_cast<int32_t>(bsz), n, s); })) return nullptr;
   return args[5] == Py_None ? THPVariable_Wrap(fresh) : same(args[5]);
   MOA_LEAVE
 }
@@ -336,12 +352,12 @@ PyObject* rule_loss(PyObject*, PyObject* const* args, Py_ssize_t nargs) {
   const float* pe = static_cast<const float*>(e->data_ptr());
   double *pd = static_cast<double*>(dl.data_ptr()), *pn = static_cast<double*>(dens.data_ptr());
   void* s = c.stream();
-  if (!call([&] {
+  if (!call(*b, [&] {
         return b->api.rule_loss(pe, static_cast<int32_t>(h), n, static_cast<int32_t>(sink), static_cast<uint32_t>(flags),
                                 static_cast<const double*>(al.v.buf), static_cast<const double*>(be.v.buf),
                                 static_cast<int32_t>(r), pd, pn, s);
       }))
-    return none();
+    return nullptr;
   PyObject* pair = PyTuple_New(2);
   if (!pair) return nullptr;
   PyTuple_SET_ITEM(pair, 0, THPVariable_Wrap(dl));
@@ -350,13 +366,15 @@ PyObject* rule_loss(PyObject*, PyObject* const* args, Py_ssize_t nargs) {
   MOA_LEAVE
 }
 
-// bind(addresses of the entry points, plan address or 0, num_q_heads, num_kv_heads, head_dim, cache rows, is bf16)
+// bind(addresses of the entry points, plan address or 0, num_q_heads, num_kv_heads, head_dim, cache rows, is bf16,
+//      function that raises for a status)
 PyObject* bind(PyObject*, PyObject* args) {
-  PyObject* table;
+  PyObject *table, *check;
   unsigned long long plan;
   long long hq, hkv, d, rows;
   int bf16;
-  if (!PyArg_ParseTuple(args, "O!KLLLLp", &PyTuple_Type, &table, &plan, &hq, &hkv, &d, &rows, &bf16)) return nullptr;
+  if (!PyArg_ParseTuple(args, "O!KLLLLpO", &PyTuple_Type, &table, &plan, &hq, &hkv, &d, &rows, &bf16, &check))
+    return nullptr;
   constexpr Py_ssize_t kEntries = sizeof(Api) / sizeof(void*);
   void* at_[kEntries];
   if (PyTuple_GET_SIZE(table) != kEntries) {
@@ -379,6 +397,7 @@ PyObject* bind(PyObject*, PyObject* args) {
   b->d = d;
   b->rows = rows;
   b->dtype = bf16 ? at::kBFloat16 : at::kFloat;
+  b->check = same(check);
   PyObject* o = PyCapsule_New(b, kName, [](PyObject* x) { delete static_cast<Bound*>(PyCapsule_GetPointer(x, kName)); });
   if (!o) delete b;
   return o;

@@ -7,8 +7,9 @@ there is no fallback.  If libmoa.so is missing, loading fails with an error.
 
 A call on plain tensors of the current device and stream is checked and made by
 the native module _binding (step append + decode: 31 us of host time before,
-10 us now); it leaves every other call, and every call that it or the library
-refuses, to the code here, which says what is wrong with it.
+10 us now); it leaves every other call, and every call that it refuses, to the
+code here, which says what is wrong with it.  A call that the library refuses, or
+that fails there, raises at once and is not made a second time.
 """
 from __future__ import annotations
 
@@ -112,7 +113,7 @@ def load_library(path: Optional[str] = None) -> ctypes.CDLL:
     from . import _binding
     _fast = _binding
     _table = tuple(ctypes.cast(getattr(lib, name), vp).value for name in _NATIVE)
-    _bound = _binding.bind(_table, 0, 0, 0, 0, 0, True)
+    _bound = _binding.bind(_table, 0, 0, 0, 0, 0, True, _check)
     _lib = lib
     return lib
 
@@ -135,7 +136,7 @@ class Plan:
         _check(load_library().moa_plan_tables(self.handle, self.window.ctypes.data,
                                               self.capacity.ctypes.data, self.offset.ctypes.data))
         self._bound = _fast.bind(_table, handle, desc.num_q_heads, hkv, desc.head_dim, self.cache_rows,
-                                 desc.dtype == MOA_BF16)
+                                 desc.dtype == MOA_BF16, _check)
 
     @property
     def num_q_heads(self) -> int:

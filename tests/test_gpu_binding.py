@@ -1,6 +1,8 @@
 """The native call path of the Python binding against its general path: the same
 results, the same refusals, and the general path wherever a call is out of the
 ordinary."""
+import ctypes
+
 import numpy as np
 import pytest
 import torch
@@ -97,3 +99,65 @@ def test_native_path_runs_on_the_current_stream():
     g.replay()
     torch.cuda.synchronize()
     assert torch.equal(o, ref) and torch.equal(p, ref)
+
+
+def _calls(dt="bf16"):
+    """name -> (its capsule, ordinary arguments of the native function, positions of the tensors in them)."""
+    plan, q, k, v = _state(dt)
+    b, n = q.shape[:2]
+    kc, vc, pc = M.new_cache(plan, b)
+    M.moa_kv_append(plan, kc, vc, pc, k, v, 0)
+    kn, vn, qd = k[:, -1:].contiguous(), v[:, -1:].contiguous(), q[:, -1].contiguous()
+    at = torch.tensor([n, n], dtype=torch.int32, device="cuda")
+    ws = M.new_workspace(plan, b)
+    alpha, beta = search.candidate_rules()
+    e = q[0, :9, 0, :2].t().float().reshape(2, 3, 3).contiguous()
+    return {
+        "moa_prefill": (plan, [q, k, v, torch.zeros_like(q)], (0, 1, 2, 3)),
+        "moa_kv_append": (plan, [kc, vc, pc, kn, vn, n], (0, 1, 2, 3, 4)),
+        "moa_kv_append_ragged": (plan, [kc, vc, pc, kn, vn, at], (0, 1, 2, 3, 4, 5)),
+        "moa_decode": (plan, [qd, kc, vc, n, ws, torch.zeros_like(qd)], (0, 1, 2, 4, 5)),
+        "moa_decode_noalloc": (plan, [qd, kc, vc, n, torch.zeros_like(qd)], (0, 1, 2, 4)),
+        "moa_decode_ragged": (plan, [qd, kc, vc, at, ws, torch.zeros_like(qd)], (0, 1, 2, 3, 4, 5)),
+        "moa_influence": (None, [q, k, v, q.flip(1).contiguous(), torch.zeros((4, 3, 3), device="cuda"), 0.0], (0, 1, 2, 3, 4)),
+        "moa_rule_loss": (None, [e, 150, 4, np.asarray(alpha), np.asarray(beta), 0], (0,)),
+    }
+
+
+NATIVE = ["moa_prefill", "moa_kv_append", "moa_decode", "moa_decode_noalloc", "moa_kv_append_ragged",
+          "moa_decode_ragged", "moa_influence", "moa_rule_loss"]
+
+
+def _public(name, plan, args, **kw):
+    return getattr(M, name)(*([] if plan is None else [plan]), *args, **kw)
+
+
+def _snapshot(args):
+    return [a.clone() for a in args if torch.is_tensor(a)]
+
+
+@pytest.mark.parametrize("name", NATIVE)
+def test_a_failed_launch_raises_and_is_not_repeated(name):
+    """The library's status reaches the caller, once: neither a second call nor a
+    silent success where the second one passes."""
+    print("[case] binding status", name, flush=True)
+    plan, args, _ = _calls()[name]
+    seen = []
+
+    @ctypes.CFUNCTYPE(ctypes.c_int)                      # looks at no argument
+    def fails():
+        seen.append(1)
+        return M.MOA_ERR_HIP
+
+    table = list(M._table)
+    table[M._NATIVE.index(name)] = ctypes.cast(fails, ctypes.c_void_p).value
+    layer = (0,) * 5 if plan is None else (plan.handle.value, plan.num_q_heads, plan.num_kv_heads, plan.head_dim,
+                                           plan.cache_rows)
+    bound = M._fast.bind(tuple(table), *layer, True, M._check)
+    before = _snapshot(args)
+    with pytest.MonkeyPatch.context() as mp:
+        mp.setattr(*((M, "_bound") if plan is None else (plan, "_bound")), bound)
+        with pytest.raises(M.MoaError) as e:
+            _public(name, plan, args)
+    assert e.value.status == M.MOA_ERR_HIP and len(seen) == 1
+    assert all(torch.equal(a, b) for a, b in zip(before, _snapshot(args)))
