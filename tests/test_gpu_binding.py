@@ -128,12 +128,57 @@ NATIVE = ["moa_prefill", "moa_kv_append", "moa_decode", "moa_decode_noalloc", "m
           "moa_decode_ragged", "moa_influence", "moa_rule_loss"]
 
 
+def _native(name, plan, args):
+    return getattr(M._fast, name[4:])(M._bound if plan is None else plan._bound, *args)
+
+
 def _public(name, plan, args, **kw):
     return getattr(M, name)(*([] if plan is None else [plan]), *args, **kw)
 
 
 def _snapshot(args):
     return [a.clone() for a in args if torch.is_tensor(a)]
+
+
+@pytest.mark.parametrize("name", NATIVE)
+def test_every_native_function_makes_the_ordinary_call(name):
+    print("[case] binding native", name, flush=True)
+    plan, args, tensors = _calls()[name]
+    plan2, args2, _ = _calls()[name]                     # the same inputs, for the general path
+    done = _native(name, plan, args)
+    assert done is not None and ("append" not in name or done is True)
+    ref = _public(name, plan2, args2, stream=torch.cuda.current_stream())
+    if name == "moa_rule_loss":
+        assert all(torch.equal(x, y) for x, y in zip(done, ref))
+    else:
+        outs = args[:3] if "append" in name else [args[tensors[-1]]]
+        refs = args2[:3] if "append" in name else [ref]
+        assert all(torch.equal(x, y) for x, y in zip(outs, refs)) and any(x.any() for x in outs)
+
+
+@pytest.mark.parametrize("name", NATIVE)
+def test_every_native_function_leaves_odd_arguments(name):
+    """Another shape, type, device or stride of any tensor: None, and nothing written."""
+    print("[case] binding odd", name, flush=True)
+    plan, args, tensors = _calls()[name]
+    for i in tensors:
+        t = args[i]
+        workspace = t.dtype == torch.uint8               # any contiguous type and length: the library looks at its bytes
+        odd = [None, t.cpu(), torch.stack((t, t), -1)[..., 0]]
+        if not workspace:
+            odd += [t.unsqueeze(0), t.long() if t.dtype == torch.int32 else t.double()]
+            odd += [torch.cat((t, t), 1 if name == "moa_rule_loss" else 0)]          # of a profile any number of heads
+        for x in odd:
+            if x is None and i == len(args) - 1 and not name.endswith(("append", "ragged", "noalloc")):
+                continue                                 # no output given: an ordinary call
+            if x is None and name in ("moa_decode_ragged", "moa_influence") and i == tensors[-1]:
+                continue
+            bad = list(args)
+            bad[i] = x
+            before = _snapshot(args)
+            assert _native(name, plan, bad) is None, (i, x if x is None else (x.shape, x.dtype, x.stride()))
+            assert all(torch.equal(a, b) for a, b in zip(before, _snapshot(args)))
+    assert _native(name, plan, args[:-1]) is None
 
 
 @pytest.mark.parametrize("name", NATIVE)
