@@ -190,16 +190,6 @@ moa_status_t moa_prefill(const moa_plan_t* plan, const void* q, const void* k, c
   const size_t kbytes = es * batch * n_tokens * d.num_kv_heads * d.head_dim;
   if (overlaps(o, qbytes, q, qbytes) || overlaps(o, qbytes, k, kbytes) || overlaps(o, qbytes, v, kbytes))
     return fail(MOA_ERR_INVALID_ARG, "moa_prefill: output overlaps an input");
-  const int64_t tiles = (n_tokens + kPrefillRows - 1) / kPrefillRows;
-  // A unit spans at least kPrefillUnitBlocks work-groups (query tiles x group),
-  // and at least kPrefillChunk query tiles.
-  const int64_t qchunk = std::min<int64_t>(std::max<int64_t>(kPrefillChunk, kPrefillUnitBlocks / plan->group), tiles);
-  const int64_t n_chunks = (tiles + qchunk - 1) / qchunk;
-  const int64_t n_units = int64_t(d.num_kv_heads) * batch * n_chunks;
-  const int64_t blocks = (n_units + kNumXcd - 1) / kNumXcd * kNumXcd * plan->group * qchunk;
-  if (blocks >= (int64_t(1) << 31))
-    return fail(MOA_ERR_UNSUPPORTED, "moa_prefill: too many work-groups for one launch");
-
   PrefillArgs a;
   memset(&a, 0, sizeof(a));
   a.q = q; a.k = k; a.v = v; a.o = o;
@@ -223,6 +213,7 @@ moa_status_t moa_prefill(const moa_plan_t* plan, const void* q, const void* k, c
   }
   const int err = d.dtype == MOA_BF16 ? launch_prefill(a, d.head_dim, hip_stream)
                                       : launch_prefill_f32(a, d.head_dim, hip_stream);
+  if (err == kGridTooLarge) return fail(MOA_ERR_UNSUPPORTED, "moa_prefill: too many work-groups for one launch");
   if (err) return fail(MOA_ERR_HIP, "moa_prefill: kernel launch failed (hipError " + std::to_string(err) + ")");
   return ok();
 }

@@ -41,7 +41,7 @@ struct PrefillArgs {
   int32_t hkv;
   int32_t group;
   int32_t num_sink;
-  int32_t n_qtiles;          // ceil(n / query rows per work-group) (these four: set by the bf16 launcher)
+  int32_t n_qtiles;          // ceil(n / query rows per work-group) (these four: set by the launcher)
   int32_t qchunk;            // query tiles per dispatch unit
   int32_t n_chunks;          // ceil(n_qtiles / qchunk)
   int32_t n_units;           // hkv * batch * n_chunks
@@ -138,7 +138,10 @@ struct RuleLossArgs {
   int32_t kv_len[kMaxRules]; // per rule: tokens its cache holds at length n, min(s + w, n)
 };
 
-// Kernel launchers (return hipError_t as int; 0 = success).
+// Kernel launchers (return hipError_t as int; 0 = success).  The prefill launchers
+// return kGridTooLarge, launching nothing, for more work-groups than one launch takes.
+constexpr int kGridTooLarge = -1;
+constexpr int64_t kMaxGrid = int64_t(1) << 31;
 int launch_prefill(const PrefillArgs& a, int head_dim, void* stream);       // bf16
 int launch_prefill_f32(const PrefillArgs& a, int head_dim, void* stream);
 int launch_kv_append(const AppendArgs& a, int dtype, int head_dim, void* stream);
@@ -149,7 +152,6 @@ int launch_rule_loss(const RuleLossArgs& a, void* stream);
 // (resolved once per device); returns a hipError_t as int.
 int decode_scratch(void** out);
 
-constexpr int kPrefillRows = 128;   // query rows per prefill work-group, where there are many
 constexpr int kPrefillChunk = 16;   // minimum query tiles per prefill dispatch unit
 constexpr int kPrefillUnitBlocks = 64;  // minimum work-groups per prefill dispatch unit
 constexpr int kNumXcd = 8;          // accelerator dies; work-groups go round-robin over them

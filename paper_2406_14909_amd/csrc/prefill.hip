@@ -544,6 +544,7 @@ template <int D, int NR, int KG>
 int launch_t(const PrefillArgs& a, void* stream) {
   PrefillArgs copy = a;
   const PrefillGrid g = prefill_grid(a, 32 * NR);
+  if (g.blocks >= kMaxGrid) return kGridTooLarge;
   copy.n_qtiles = static_cast<int32_t>(g.tiles);
   copy.qchunk = static_cast<int32_t>(g.qchunk);
   copy.n_chunks = static_cast<int32_t>(g.n_chunks);

@@ -557,6 +557,7 @@ __global__ void __launch_bounds__(NW * 64, 2) prefill_f32_shared_kernel(PrefillA
 int launch_shared(const PrefillArgs& a, void* stream) {
   PrefillArgs copy = a;
   const PrefillGrid g = prefill_grid(a, SharedTiles<64>::BM);
+  if (g.blocks >= kMaxGrid) return kGridTooLarge;
   copy.n_qtiles = static_cast<int32_t>(g.tiles);
   copy.qchunk = static_cast<int32_t>(g.qchunk);
   copy.n_chunks = static_cast<int32_t>(g.n_chunks);
@@ -573,7 +574,7 @@ int launch_t(const PrefillArgs& a, void* stream) {
   int64_t pairs = int64_t(a.hkv) * a.batch;
   if (pairs >= kPairsPerDie * kNumXcd) pairs = (pairs + kNumXcd - 1) / kNumXcd * kNumXcd;
   const int64_t blocks = (a.n + rows - 1) / rows * pairs * a.group;
-  if (blocks >= (int64_t(1) << 31)) return static_cast<int>(hipErrorInvalidValue);
+  if (blocks >= kMaxGrid) return kGridTooLarge;
   PrefillArgs copy = a;
   void* args[] = {&copy};
   return static_cast<int>(hipLaunchKernel(reinterpret_cast<const void*>(&prefill_f32_kernel<D, KG, RW>),

@@ -25,6 +25,10 @@ inline PrefillGrid prefill_grid(const PrefillArgs& a, int rows) {
   g.qchunk = std::min<int64_t>(std::max<int64_t>(kPrefillChunk, kPrefillUnitBlocks / a.group), g.tiles);
   g.n_chunks = (g.tiles + g.qchunk - 1) / g.qchunk;
   g.n_units = int64_t(a.hkv) * a.batch * g.n_chunks;
+  if (g.n_units >= kMaxGrid) {
+    g.per_die = g.blocks = kMaxGrid;
+    return g;
+  }
   g.per_die = (g.n_units + kNumXcd - 1) / kNumXcd * a.group * g.qchunk;
   g.blocks = g.per_die * kNumXcd;
   return g;

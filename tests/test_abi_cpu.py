@@ -148,6 +148,18 @@ def test_plan_null_arguments():
     assert lib.moa_decode_workspace_bytes(None, 4) == 0
 
 
+@pytest.mark.parametrize("dtype,d,hkv,batch", [("bf16", 64, 8, 64), ("bf16", 128, 8, 64), ("f32", 64, 8, 64), ("f32", 128, 8, 64),
+                                               ("f32", 128, 7, 73), ("f32", 64, 64, 1 << 30), ("bf16", 128, 64, 1 << 30)])
+def test_prefill_rejects_more_work_groups_than_a_launch_takes(dtype, d, hkv, batch):
+    """2^31 work-groups or more by the grid of the kernel that would run (fp32: 7 KV
+    heads x 73 sequences are dealt to the dies as 512 pairs)."""
+    p = _plan([100.0] * hkv, [0.0] * hkv, 1024, 4, hq=hkv, hkv=hkv, d=d, dtype=dtype)
+    n = 1 << 29
+    far = 1 << 60 if batch > 1000 else 1 << 50           # apart, never dereferenced
+    st = lib.moa_prefill(p.handle, far, 2 * far, 3 * far, 4 * far, batch, n, None)
+    assert (st, "too many work-groups" in lib.moa_last_error().decode()) == (M.MOA_ERR_UNSUPPORTED, True)
+
+
 def test_gpu_entry_points_validate_before_launch():
     # Every call below is invalid and must return before touching the GPU.
     p = _plan([100.0, 200.0], [0.0, 0.0], 1024, 4, hq=4, hkv=2)
