@@ -398,7 +398,7 @@ def main() -> int:
             "bytes_per_launch": round(timed_bytes / len(timed)),
         },
         "roofline_prefill": {
-            "kernel": "prefill_kernel<bf16,128>, per call",
+            "kernel": f"prefill_kernel<{D},4,1>, per call",
             "bound": "mfma",
             "achieved": round(pre_tflops, 2),
             "peak": BF16_MFMA_PEAK_TFLOPS,
@@ -491,7 +491,7 @@ def measure_configs(M, workloads, reps: int):
             tf = flops / (ms / 1e3) / 1e12
             entry["prefill"] = {"batch": B, "ms": round(ms, 4), "inband_tflops": round(tf, 2),
                                 "peak": BF16_MFMA_PEAK_TFLOPS, "frac": round(tf / BF16_MFMA_PEAK_TFLOPS, 4),
-                                "flops_per_launch": flops, "kernel": f"prefill_kernel<bf16,{D}>",
+                                "flops_per_launch": flops, "kernel": f"prefill_kernel<{D},4,1>",
                                 "calls_timed": n_calls}
             del q, k, v, o
         if do_decode:

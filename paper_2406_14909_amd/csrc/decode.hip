@@ -77,12 +77,11 @@ int decode_scratch(void** out) {
 namespace {
 
 constexpr int kWaves = 4;          // waves per worker (work-group)
-// Keys per wave tile in the matrix-core loop: 32 (8 KB of LDS per wave, about
-// 160 VGPRs at group 4 and 226 at group 8).  At group 8 the earlier 64-key
-// tiles (2 work-groups per compute unit) measured 2.8 % slower than 32-key
-// tiles once K no longer came in operand layout from HBM.
-template <int G>
-constexpr int mma_keys() { return 32; }
+// Keys per wave tile in the matrix-core loop: 32 (8 KB of LDS per wave, 162 VGPRs
+// at head_dim 128, three work-groups per compute unit).  At group 8 64-key tiles
+// with two work-groups measured 2.8 % slower once K no longer came in operand
+// layout from HBM.
+constexpr int kMmaKeys = 32;
 
 __device__ __forceinline__ int uniform(int x) { return __builtin_amdgcn_readfirstlane(x); }
 
@@ -335,9 +334,9 @@ __device__ __forceinline__ float dot2_ones(bf16 a, bf16 b, float acc) {
 #endif
 }
 
-template <int D, int KEYS>
+template <int D>
 struct MmaTile {
-  static constexpr int KT = KEYS;
+  static constexpr int KT = kMmaKeys;
   static constexpr int KS = D / 32;           // S steps over the head dimension
   static constexpr int DT = D / 16;           // 16-row output tiles of O^T
   static constexpr int RB = D * 2;            // bytes per cache row
@@ -349,8 +348,8 @@ struct MmaTile {
 };
 
 template <int D, int G>
-__global__ void __launch_bounds__(kWaves * 64, mma_keys<G>() == 32 ? 3 : 2) decode_mma_kernel(DecodeArgs a) {
-  using TL = MmaTile<D, mma_keys<G>()>;
+__global__ void __launch_bounds__(kWaves * 64, 3) decode_mma_kernel(DecodeArgs a) {
+  using TL = MmaTile<D>;
   constexpr int KT = TL::KT, KS = TL::KS, DT = TL::DT, RB = TL::RB, CPR = TL::CPR, VLD = TL::VLD;
   constexpr int NST = KT / 16, NKS = KT / 32;   // 16-key score tiles, 32-key PV steps per wave tile
   static_assert(KT % 32 == 0, "whole 32-key steps");
@@ -637,7 +636,7 @@ template <typename T, int D, int G>
 int launch_t(DecodeArgs a, void* stream) {
   constexpr bool kMma = sizeof(T) == 2 && G >= 2;
   // Keys that a worker's waves read at once: one round of its loop.
-  constexpr int kRound = kMma ? kWaves * mma_keys<G>() : kWaves * 8 * (64 / (D / Vec16<T>::N));
+  constexpr int kRound = kMma ? kWaves * kMmaKeys : kWaves * 8 * (64 / (D / Vec16<T>::N));
   const void* kernel;
   if constexpr (kMma) kernel = reinterpret_cast<const void*>(&decode_mma_kernel<D, G>);
   else kernel = reinterpret_cast<const void*>(&decode_valu_kernel<T, D, G>);

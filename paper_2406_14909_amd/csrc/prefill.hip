@@ -176,16 +176,12 @@ __global__ void __launch_bounds__(NR * KG * 64, D == 128 && NR * KG == 4 && KG >
   // is issued, see the pipeline prologue).
   bf16x8 qf[KS];
 
-  // Direct-to-LDS tile loads: DMA instruction I writes buffer bytes
-  // [I*1024, I*1024 + 1024) and lane L's 16 bytes land at chunk I*64 + L.
-  // Chunk m is row m / CPR, position p = m % CPR, and carries global chunk
-  // p ^ swz(row).  Keys past the end re-read the last key (always masked by
-  // causality).
-  // Per-lane byte offsets of the DMA sources relative to the tile's first key
-  // row (tile independent).  DMA instruction I writes tile bytes
+  // Direct-to-LDS tile loads: per-lane byte offsets of the sources relative to the
+  // tile's first key row (tile independent).  Instruction I writes tile bytes
   // [I*1024, I*1024 + 1024): lane L's 16 bytes land at chunk m = I*64 + L, i.e.
   // row m / CPR, chunk position m % CPR, and carry global chunk
-  // position ^ swz(row).  Wave w issues instructions w*DMA_PER_WAVE + i.
+  // position ^ swz(row).  Wave w issues instructions w*DMA_PER_WAVE + i.  Keys
+  // past the end re-read the last key (always masked by causality).
   constexpr int DPW = TL::DMA_PER_WAVE;
   uint32_t k_src[DPW], v_src[DPW];
   auto dma_row = [&](int i) { return ((wave * DPW + i) * 64 + lane) / CPR; };
