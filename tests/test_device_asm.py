@@ -11,6 +11,9 @@ library's own flags (no GPU needed).
 * No flat loads or stores: a load that may go to two kinds of memory is waited
   for with everything else in flight (a choice between a kernel argument and a
   device array once became one, before every cache of a decode call).
+* The merge of decode asks for all the partials of a pass before it waits for
+  the first (a skipped partial's loads once sank into a branch, one trip to
+  memory after the other).
 * No packed fp32 VALU forms are emitted (they are kept out of every kernel by
   the build flags).
 """
@@ -84,3 +87,14 @@ def test_no_packed_fp32_forms(src, device_asm):
 def test_no_flat_memory_access(src, device_asm):
     found = [t for t in _instructions(device_asm(src)) if re.match(r"flat_(load|store|atomic)", t)]
     assert not found, f"{src}: {len(found)} flat accesses, first {found[0]!r}"
+
+
+def test_merge_loads_are_in_flight_together(device_asm):
+    bodies = re.findall(r"\n(_ZN\w*decode_combine_kernel\w*):[^\n]*\n(.*?)\.Lfunc_end", device_asm("decode.hip"), re.S)
+    assert len(bodies) == 16                                # bf16 and fp32, two head sizes, four group sizes
+    for name, body in bodies:
+        ins = list(_instructions(body))
+        loads = [i for i, t in enumerate(ins) if t.startswith("global_load")]
+        assert len(loads) == 8, f"{name}: {len(loads)} loads"   # a statistics pair and a float4 of four partials
+        between = [t for t in ins[loads[0]:loads[-1]] if re.match(r"s_cbranch|s_branch|s_waitcnt.*vmcnt", t)]
+        assert not between, f"{name}: {between}"
