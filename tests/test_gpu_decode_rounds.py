@@ -24,7 +24,11 @@ CASES = [
     ("bf16", 32, 32, 128, 16, 0, tuple(range(4000, 4320, 10)), 5000),   # pieces of many rounds
     ("bf16", 32, 4, 64, 24, 3, (5000, 3, 1021, 2045), 7000),
     ("bf16", 16, 8, 128, 4, 0, (3072,) * 7 + (3073,), 5000),            # a little over a round per slot: two each
-    ("bf16", 64, 8, 128, 8, 4, (4090, 4093) * 4, 5000),                 # over two: equal numbers of keys
+    ("bf16", 64, 8, 128, 8, 4, (4090, 4093) * 4, 5000),                 # over two: rounds dealt
+    ("bf16", 64, 8, 128, 8, 4, (4090,) * 8, 5000),                      # equal numbers of keys
+    ("bf16", 8, 1, 128, 1, 0, (32769,), 40000),                         # 129 partials for the merge
+    ("bf16", 2, 2, 64, 2, 5, (66000, 33000), 70000),                    # 130 and fewer
+    ("f32", 4, 2, 64, 1, 0, (33000, 9000), 40000),
 ]
 
 
