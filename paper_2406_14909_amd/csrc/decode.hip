@@ -10,9 +10,10 @@
 // Work split.  The caches differ in length by orders of magnitude across
 // heads, so the work is not cut per cache: all filled slots of the batch,
 // laid end to end in (sequence, KV head) order, form one virtual key range
-// that is cut into equal pieces, one per work-group ("worker"), with at most
-// as many workers as the chip holds resident work-groups (decode_split.h).  A
-// worker walks its piece cache by cache; its 4 waves take interleaved rows (or tiles) of each cache
+// that is cut into pieces of equal length, to one round of the kernel's loop or
+// one key, one per work-group ("worker"), with at most as many workers as the
+// chip holds resident work-groups (decode_split.h).  A worker walks its piece
+// cache by cache; its 4 waves take interleaved rows (or tiles) of each cache
 // and keep an online softmax (base 2, running max m, running sum l,
 // unnormalised output acc) for all G query heads of the KV head, so each K/V
 // byte is read from HBM once; the waves' states are merged through LDS at the

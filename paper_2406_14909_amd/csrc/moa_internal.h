@@ -156,7 +156,7 @@ constexpr int kPrefillChunk = 16;   // minimum query tiles per prefill dispatch 
 constexpr int kPrefillUnitBlocks = 64;  // minimum work-groups per prefill dispatch unit
 constexpr int kNumXcd = 8;          // accelerator dies; work-groups go round-robin over them
 constexpr int64_t kLastLevelCacheBytes = int64_t(256) << 20;   // MI355X Infinity Cache
-constexpr int kMaxDecodeWorkers = 8192;  // decode workers (waves) per launch, at most
+constexpr int kMaxDecodeWorkers = 8192;  // decode workers (work-groups) per launch, at most
 constexpr int kDecodePartPad = 4;        // partial row: head_dim sums, m, l, 2 pad floats
 constexpr size_t kDecodeScratchBytes = MOA_DECODE_SCRATCH_BYTES;   // library-owned decode workspace per GPU
 constexpr int kInfluenceBlock = 64;      // profiling block (tokens)
